@@ -69,7 +69,7 @@ def expert_bytes(shape, F: int) -> int:
 
 
 FFN_SOURCES = {
-    "bf16": ["ffn_bf16.hip", "ffn_common.h", "common.h", "kernels.h"],
+    "bf16": ["ffn_bf16.hip", "ffn_bf16_wide.hip", "ffn_common.h", "common.h", "kernels.h"],
     "q4g32": ["ffn_q4.hip", "ffn_common.h", "common.h", "kernels.h"],
     "f32": ["ffn.hip", "ffn_common.h", "common.h", "kernels.h"],
 }

@@ -2,11 +2,15 @@
 //
 // Unit of work: R consecutive 16-row tiles of one expert matrix pair (gate
 // and up) or one down matrix, for all tokens routed to that expert.  The W
-// waves of the workgroup split the reduction dimension K into W contiguous
-// ranges; each wave streams its range with a double-buffered register
+// waves of the workgroup split the reduction dimension K, dealt in runs of
+// two or more steps so that the waves read consecutive kilobytes of a row
+// tile at a time; each wave streams its share with a double-buffered register
 // pipeline (the next chunk of steps is in flight while the current one
 // feeds the MFMAs), and the W partial tiles are added through LDS in wave
-// order, so results do not depend on timing.
+// order, so results do not depend on timing.  Dealt runs against one
+// contiguous range per wave, step times on MI355X: H = 4096, F = 14336 at
+// 6 / 16 / 32 / 64 tokens 275 / 350 / 430 / 441 -> 269 / 348 / 391 / 432 us,
+// row-major H = F = 2880 at 10 / 20 tokens 181 / 299 -> 170 / 285 us.
 //
 // Per 32-wide K step a lane loads 16 bytes of each of its R weight rows (the
 // A operand of v_mfma_f32_16x16x32_bf16: row = lane % 16, K slice =
@@ -80,7 +84,6 @@ __device__ __forceinline__ void unit_pass(const FfnArgs& a, const Segment& seg, 
   const int wave = wave_id();
   const int rA = lane & 15, gK = lane >> 4;
   const int nks = K / 32;
-  const int lo = wave * nks / W, hi = (wave + 1) * nks / W;
 
   const uint16_t* X = static_cast<const uint16_t*>(kMode == 0 ? a.x : a.hh);
   const int ldx = kMode == 0 ? a.H : a.ldh;
@@ -111,11 +114,16 @@ __device__ __forceinline__ void unit_pass(const FfnArgs& a, const Segment& seg, 
     for (int r = 0; r < R; ++r)
 #pragma unroll
       for (int tt = 0; tt < T; ++tt) acc[m][r][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (hi > lo) {
+  // Stage c of the wave: K is dealt to the waves in runs of at least two steps.
+  constexpr int kRun = U >= 2 ? 1 : 2;  // stages per run
+  auto step_of = [&](int c) { return ((c / kRun * W + wave) * kRun + c % kRun) * U; };
+  const int n_stages = (nks + U - 1) / U, rounds = n_stages / (kRun * W);
+  const int left = n_stages - rounds * kRun * W - wave * kRun;
+  const int n = rounds * kRun + min(max(left, 0), kRun);
+  if (n > 0) {
     pipeline2<Stage<T, R, NM, U>>(
-        (hi - lo + U - 1) / U,
-        [&](Stage<T, R, NM, U>& st, int c) { load_stage<kPacked>(st, pa, xb, lo + c * U, hi); },
-        [&](const Stage<T, R, NM, U>& st, int c) { compute_stage(st, acc, lo + c * U, hi); });
+        n, [&](Stage<T, R, NM, U>& st, int c) { load_stage<kPacked>(st, pa, xb, step_of(c), nks); },
+        [&](const Stage<T, R, NM, U>& st, int c) { compute_stage(st, acc, step_of(c), nks); });
   }
 
   if (W > 1) {
@@ -262,7 +270,6 @@ __global__ __launch_bounds__(1024) void ffn_bf16_down_combine_kernel(FfnArgs a,
   if (live) {
     const int K = seg.shared ? a.Fs : a.F;
     const int nks = K / 32;
-    const int lo = part * nks / KW, hi = (part + 1) * nks / KW;
     const uint16_t* W0 = static_cast<const uint16_t*>(seg.shared ? a.sh_down : a.down) +
                          (size_t)seg.id * a.H * K;
     const u32x4* xb[1];
@@ -278,11 +285,12 @@ __global__ __launch_bounds__(1024) void ffn_bf16_down_combine_kernel(FfnArgs a,
       else
         pa[r] = reinterpret_cast<const u32x4*>(W0 + (size_t)(r0 + 16 * r + rA) * K) + gK;
     }
-    if (hi > lo) {
+    const int first = part * U;
+    if (nks > first) {
       pipeline2<Stage<1, R, 1, U>>(
-          (hi - lo + U - 1) / U,
-          [&](Stage<1, R, 1, U>& st, int c) { load_stage<kPacked>(st, pa, xb, lo + c * U, hi); },
-          [&](const Stage<1, R, 1, U>& st, int c) { compute_stage(st, acc, lo + c * U, hi); });
+          (nks - first + KW * U - 1) / (KW * U),
+          [&](Stage<1, R, 1, U>& st, int c) { load_stage<kPacked>(st, pa, xb, first + c * KW * U, nks); },
+          [&](const Stage<1, R, 1, U>& st, int c) { compute_stage(st, acc, first + c * KW * U, nks); });
     }
   }
   small_down_finish<R, KW>(a, seg, live, part, members, acc, lds, y, r0);
@@ -336,7 +344,8 @@ hipError_t launch_mode(const FfnArgs& a, int spw, hipStream_t s) {
 // For 17-32 tokens the down projection (a short K: 24 steps at F = 768)
 // splits K over 4 waves of 6 steps: measured on MI355X at 32 tokens over
 // 128 experts, its launch then takes 2 us less than with one wave (8 waves:
-// 15 us more).
+// 15 us more).  For 33 tokens and more two waves split every K, also a short
+// one, as the wide kernel does.
 #ifndef S2MOE_BF16_TINY
 #define S2MOE_BF16_TINY 1, 1, 2, 1, 4, 16
 #endif
@@ -347,7 +356,7 @@ hipError_t launch_mode(const FfnArgs& a, int spw, hipStream_t s) {
 #define S2MOE_BF16_MEDIUM 2, 2, 2, 2, 2, 32, 4
 #endif
 #ifndef S2MOE_BF16_LARGE
-#define S2MOE_BF16_LARGE 4, 2, 1, 4, 1, 16
+#define S2MOE_BF16_LARGE 4, 2, 1, 4, 1, 1
 #endif
 
 template <int TMAX, int RG, int UG, int RD, int UD, int SPW, int SPWD = SPW>
@@ -427,9 +436,23 @@ hipError_t launch_moe_layer_small_bf16(const RouteArgs& ra, const GateArgs& ga,
                   : TinyLayer::layer<false>(ra, ga, a, y, s);
 }
 
+// Batches of more tokens than this run on ffn_bf16_wide.hip.  Step times on
+// MI355X, this file's kernel against it: packed weights, H = 4096,
+// F = 14336, 8 experts at 64 / 80 / 128 / 256 tokens 431 / 457 / 573 / 955
+// against 454 / 461 / 487 / 559 us; 128 experts of F = 768 at 70 / 128 tokens
+// 131 / 176 against 134 / 166 us.  Row-major weights, where 32-row units read
+// 128 bytes of a row at a time: 37 tokens at H = F = 2880, 128 experts 395
+// against 351 us, 48 tokens at F = 1024, 64 experts 142 against 137 us, but
+// 24 tokens at F = 768 105 against 107 us.  Up to kWideMinPacked both layouts
+// add the same two K parts in the same order, so their results stay equal
+// bit for bit.
+constexpr int kWideMinPacked = 96;
+constexpr int kWideMinRows = 32;
+
 hipError_t launch_ffn_bf16(const FfnArgs& a, hipStream_t s) {
   if (a.B <= 4) return launch_bf16_pair<S2MOE_BF16_TINY>(a, s);
   if (a.B <= 16) return launch_bf16_pair<S2MOE_BF16_SMALL>(a, s);
+  if (a.B > (a.packed ? kWideMinPacked : kWideMinRows)) return launch_ffn_bf16_wide(a, s);
   if (a.B <= 32) return launch_bf16_pair<S2MOE_BF16_MEDIUM>(a, s);
   return launch_bf16_pair<S2MOE_BF16_LARGE>(a, s);
 }

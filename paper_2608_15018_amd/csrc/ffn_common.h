@@ -35,11 +35,12 @@ __device__ __forceinline__ bool resolve_block(const FfnArgs& a, int mode, int ro
   bid -= a.S * nbs;
   const int u = bid / nbr;
   *rb = bid % nbr;
-  if (u >= min(*a.n_uniq, min(a.E, a.B * a.k))) return false;
-  // The routing arrays come from the gating step; values outside their
-  // ranges (routing never computed) make the block idle instead of faulting.
-  const int e = a.uniq[u];
-  if (e < 0 || e >= a.E) return false;
+  // The grid covers u < min(E, B k), so uniq[u] is loaded beside n_uniq
+  // without waiting for it.  The routing arrays come from the gating step;
+  // values outside their ranges (routing never computed) make the block idle
+  // instead of faulting.
+  const int e = a.uniq[u], nu = *a.n_uniq;
+  if (u >= min(nu, min(a.E, a.B * a.k)) || e < 0 || e >= a.E) return false;
   seg->shared = false;
   seg->id = e;
   seg->n = a.count[e];

@@ -211,6 +211,7 @@ hipError_t launch_pack(const PackArgs& a, hipStream_t s);
 hipError_t launch_reuse_gate(const GateArgs& a, hipStream_t s);
 hipError_t launch_ffn(const FfnArgs& a, hipStream_t s);
 hipError_t launch_ffn_bf16(const FfnArgs& a, hipStream_t s);
+hipError_t launch_ffn_bf16_wide(const FfnArgs& a, hipStream_t s);
 hipError_t launch_ffn_q4(const FfnArgs& a, hipStream_t s);
 hipError_t launch_combine(const CombineArgs& a, hipStream_t s);
 // int4 weights with K parts and defer_reduce: the parts' ordered reduce into
