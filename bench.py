@@ -193,14 +193,24 @@ def _head_start():
     torch.cuda._sleep(5_000_000)
 
 
-def expand_bytes(d: dict, L: int, k: int) -> int:
-    """Algorithmic HBM bytes of one s2moe_expand launch: each tree's node
-    records (parent, q, C^draft: 12 B) and predicted expert ids (L*k int32)
-    for its n_t nodes, the root's ids and n_nodes read once; order, util and
-    n_new (16 B per padded node) and the three per-tree counts written."""
+def expand_bytes(d: dict, L: int, k: int, t_ar: float) -> int:
+    """HBM bytes that one s2moe_expand launch needs: each tree's node records
+    (parent, q, C^draft: 12 B) for its n_t nodes, the predicted expert ids
+    (L*k int32) of the nodes that could be selected (p_i T_AR / C^draft >= 1
+    for the node and all its ancestors), the root's ids and n_nodes read once;
+    order, util and n_new (16 B per padded node) and the three per-tree counts
+    written."""
     T, N = d["parent"].shape
     nodes = int(d["n_nodes"].sum())
-    return nodes * (12 + 4 * L * k) + T * (4 * L * k + 4) + T * N * 16 + T * 12
+    p = np.zeros((T, N))
+    tree = np.arange(T)
+    for i in range(N):
+        par = d["parent"][:, i]
+        above = np.where(par < 0, 1.0, p[tree, np.maximum(par, 0)])
+        v = above * d["q"][:, i]
+        p[:, i] = np.where((i < d["n_nodes"]) & (v * t_ar / d["c_draft"][:, i] >= 1.0), v, 0.0)
+    viable = int((p > 0).sum())
+    return nodes * 12 + viable * 4 * L * k + T * (4 * L * k + 4) + T * N * 16 + T * 12
 
 
 def bench_expand(args) -> int:
@@ -231,7 +241,7 @@ def bench_expand(args) -> int:
     # Timed: K back-to-back launches between one pair of HIP events on the
     # launch stream, cycling through copies of the trees that together exceed
     # the 256 MB Infinity Cache, so every launch reads its ids from HBM.
-    nbytes = expand_bytes(d, L, k)
+    nbytes = expand_bytes(d, L, k, wl.t_ar)
     copies = 1 if args.no_scrub else max(1, min(64, -(-ROTATE_BYTES // nbytes)))
     devs = [dev] + [{kk: v.clone() for kk, v in dev.items()} for _ in range(copies - 1)]
     for dd in devs:

@@ -459,7 +459,7 @@ s2moe_status s2moe_expand_max_nodes(int32_t n_layers, int32_t n_experts, int32_t
   if ((st = device_lds(fn, &lds)) != S2MOE_OK) return st;
   int best = 0;
   for (int n = 1; n <= 1024; ++n)
-    if (s2moe::expand_lds(n, n_layers, n_experts, k).total <= lds) best = n;
+    if (s2moe::expand_accept_bytes(n, n_layers, n_experts) <= lds) best = n;
   *max_nodes = best;
   return ok();
 }
@@ -498,7 +498,7 @@ s2moe_status s2moe_expand(const s2moe_expand_shape* shape, const int32_t* parent
   if (root_eid != nullptr && !aligned(root_eid, 4))
     return fail(S2MOE_EINVAL, "%s: root_eid is not 4-byte aligned", fn);
   if (!aligned(eid, 16)) return fail(S2MOE_EINVAL, "%s: eid is not 16-byte aligned", fn);
-  const size_t need = s2moe::expand_lds(sh.max_nodes, sh.n_layers, sh.n_experts, sh.k).total;
+  const size_t need = s2moe::expand_accept_bytes(sh.max_nodes, sh.n_layers, sh.n_experts);
   size_t lds = 0;
   if ((st = device_lds(fn, &lds)) != S2MOE_OK) return st;
   if (need > lds)
@@ -508,7 +508,8 @@ s2moe_status s2moe_expand(const s2moe_expand_shape* shape, const int32_t* parent
                 fn, sh.max_nodes, sh.n_layers, sh.n_experts, sh.k, need, lds);
   // f / k for f < N L k <= 2^22 as one multiply and shift: the error of
   // f * ceil(2^42 / k) / 2^42 is below f / 2^42 <= 2^-20 < 1 / k.
-  const uint64_t kdiv = ((1ull << 42) + (uint64_t)sh.k - 1) / (uint64_t)sh.k;
+  const auto div42 = [](uint64_t d) { return ((1ull << 42) + d - 1) / d; };
+  const uint64_t cpn = ((uint64_t)sh.n_layers * (uint64_t)sh.k + 3) / 4;
   s2moe::ExpandArgs a{};
   a.parent = parent;
   a.q = q;
@@ -528,10 +529,11 @@ s2moe_status s2moe_expand(const s2moe_expand_shape* shape, const int32_t* parent
   a.E = sh.n_experts;
   a.k = sh.k;
   a.max_admit = sh.max_admit;
-  a.k_div = kdiv;
+  a.k_div = div42((uint64_t)sh.k);
+  a.cpn_div = div42(cpn);
   a.t_ar = sh.t_ar;
   a.t_exp = sh.t_exp;
-  return hip_status(fn, s2moe::launch_expand(a, need, static_cast<hipStream_t>(stream)));
+  return hip_status(fn, s2moe::launch_expand(a, lds, static_cast<hipStream_t>(stream)));
 }
 
 s2moe_status s2moe_stream_read(const void* src, size_t bytes, uint32_t* sink, void* stream) {

@@ -155,16 +155,20 @@ struct ExpandArgs {
   int32_t* n_pairs;         // [T]
   int32_t* status;          // [T]
   int T, N, L, E, k, max_admit;
-  uint64_t k_div;  // ceil(2^42 / k): f / k == (f * k_div) >> 42 for f < 2^22, k <= 32
+  uint64_t k_div;    // ceil(2^42 / k): f / k == (f * k_div) >> 42 for f < 2^22, k <= 32
+  uint64_t cpn_div;  // the same for ceil(L k / 4), the 4-id chunks of a node (<= 1024)
+  int cap;           // nodes of a tree whose bitsets are kept in LDS (set by launch_expand)
+  int pass;          // which trees the launch takes (set by launch_expand)
   double t_ar, t_exp;
 };
 
 // Byte offsets of the expansion kernel's LDS regions; host and device use
 // the same function so the launch size and the carve-up agree.
 struct ExpandLds {
-  int ew;  // words of one layer's expert bitset, ceil(E / 32) rounded up to a power of two
-  size_t ben, rows, uni, cdr, front, misc, state, total;
+  size_t pv, rows, uni, cdr, node, slot, par, list, misc, total;
 };
+
+constexpr int kExpandWaves = 4;  // waves of a workgroup
 
 __host__ __device__ inline int expand_words(int E) {
   int w = 1;
@@ -172,29 +176,40 @@ __host__ __device__ inline int expand_words(int E) {
   return w;
 }
 
-__host__ __device__ inline ExpandLds expand_lds(int N, int L, int E, int k) {
-  (void)k;
+// Layout for N nodes with the expert bitsets of `cap` of them.
+__host__ __device__ inline ExpandLds expand_lds(int N, int L, int E, int cap) {
+  const size_t row = (size_t)L * expand_words(E) * 4;
   ExpandLds o;
-  o.ew = expand_words(E);
   size_t off = 0;
-  o.ben = off;    off += (size_t)N * 8;              // p_i, then B_i (double)
+  o.misc = off;   off += 256;                        // reductions and counters
+  o.pv = off;     off += (size_t)N * 8;              // p_i (double)
   off = (off + 15) & ~(size_t)15;
-  o.rows = off;   off += (size_t)N * L * o.ew * 4;   // expert bitset per (node, layer)
-  o.uni = off;    off += (size_t)L * o.ew * 4;       // union bitset per layer
+  o.rows = off;   off += (size_t)cap * row;          // expert bitset per (slot, layer)
+  off = (off + 15) & ~(size_t)15;
+  o.uni = off;    off += kExpandWaves * row;         // union bitset per layer, per wave
   o.cdr = off;    off += (size_t)N * 4;              // C^draft
-  o.front = off;  off += (size_t)N * 4;              // candidate list
-  off = (off + 15) & ~(size_t)15;
-  o.misc = off;   off += 128;                        // reductions and counters
-  o.state = off;  off += (size_t)N;                  // per-node flags
+  o.node = off;   off += (size_t)N * 2;              // node of a slot
+  o.slot = off;   off += (size_t)N * 2;              // slot of a node
+  o.par = off;    off += (size_t)N * 2;              // parent node of a slot
+  o.list = off;   off += kExpandWaves * (size_t)N * 2;  // candidate list, per wave
   o.total = (off + 15) & ~(size_t)15;
   return o;
+}
+
+// LDS bytes by which a tree shape is accepted: bitsets of all N nodes and
+// of one union, 17 bytes per node and 128 of counters.
+inline size_t expand_accept_bytes(int N, int L, int E) {
+  const size_t row = (size_t)L * expand_words(E) * 4;
+  const size_t bits = (((size_t)N * 8 + 15) & ~(size_t)15) + (size_t)(N + 1) * row + (size_t)N * 8;
+  return (((bits + 15) & ~(size_t)15) + 128 + (size_t)N + 15) & ~(size_t)15;
 }
 
 // Device address of the library's scratch array on the current device
 // (S2MOE_NOALLOC_SCRATCH_BYTES bytes, 256-byte aligned).
 hipError_t noalloc_scratch(void** ptr);
 
-hipError_t launch_expand(const ExpandArgs& a, size_t lds_bytes, hipStream_t s);
+// lds_limit: LDS available to a workgroup.
+hipError_t launch_expand(const ExpandArgs& a, size_t lds_limit, hipStream_t s);
 hipError_t launch_route(const RouteArgs& a, hipStream_t s);
 // Logits only (the first launch of launch_route's small-batch path).
 hipError_t launch_route_rows(const RouteArgs& a, hipStream_t s);
