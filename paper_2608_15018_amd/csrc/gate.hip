@@ -8,13 +8,17 @@
 //   * g: a few threads per expert sum runs of tokens, runs added in order;
 //   * TopCap: one wave's exact top-cap of the candidates' g by (g desc, id
 //     asc), the threshold search used for the per-token top-k;
-//   * per token (one wave, up to 4 tokens at a time): biased order keys, an
-//     exact top-k (a bitwise threshold search over the upper key halves,
-//     then the boundary bucket ranked; ties to the lower expert id), ballot
-//     ranks for ascending-id order, DPP softmax;
+//   * per token (a team of lanes: a wave, or a 16-lane row of one so that the
+//     workgroup takes 64 tokens at a time): biased order keys, the exact top-k
+//     by taking the team's largest key k times (ties to the lower expert id),
+//     a scan for ascending-id order, a softmax over the team;
 //   * buckets: a B-bit token mask per expert (LDS 64-bit ORs), so an
 //     assignment's position in its expert's list is the popcount of the mask
 //     below its token.
+// Measured on MI355X, this kernel: 256 tokens over 8 experts 25 -> 10.6 us, 64
+// over 64 experts 11.1 -> 8.3, 37 over 128 experts 12.5 -> 9.6, against a
+// bitwise threshold search by ballots, one token per wave at a time, which the
+// one scalar unit of the compute unit bound.
 // Every result is deterministic: integer atomics only (bitwise OR), fixed
 // floating-point summation orders, rank-based placement.
 #include "small_batch.h"
@@ -23,17 +27,36 @@ namespace s2moe {
 
 constexpr int kStage = 10240;  // logits staged in LDS up to B * E = 10240
 
-// kNJ = expert slots per lane (E <= 64 kNJ); kNT = tokens a wave takes
-// through the threshold search together.  kSelect (with kStaged): the
-// kernel first ranks every token's staged logits itself (wave_select_plain,
-// the routing kernel's code, one wave per token) and writes plain_idx and
-// gap, instead of reading them from a routing launch (ra: the routing
-// step's arguments).
-template <bool kStaged, int kNJ, int kNT, bool kSelect>
+// A token's logits in this lane's slots (experts e0 .. e0 + S - 1); slots past
+// E are left 0.
+template <int S>
+__device__ __forceinline__ void load_row(const float* ell, int e0, int E, bool real, float (&l)[S]) {
+  if (S % 4 == 0 && (E & 3) == 0) {
+#pragma unroll
+    for (int s = 0; s < S; s += 4) {
+      const f32x4 v = real && e0 + s < E ? *reinterpret_cast<const f32x4*>(ell + e0 + s)
+                                         : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (s + q < S) l[s + q] = v[q];
+    }
+  } else {
+#pragma unroll
+    for (int s = 0; s < S; ++s) l[s] = real && e0 + s < E ? ell[e0 + s] : 0.f;
+  }
+}
+
+// kG = lanes of a token's team, kS = expert slots per lane (E <= kG kS).
+// kSelect (with
+// kStaged): the kernel first ranks every token's staged logits itself and
+// writes plain_idx and gap, instead of reading them from a routing launch
+// (ra: the routing step's arguments).
+template <bool kStaged, int kG, int kS, bool kSelect>
 __global__ __launch_bounds__(1024) void reuse_gate_kernel(GateArgs a, RouteArgs ra) {
   static_assert(kStaged || !kSelect, "ranking reads the staged logits");
   constexpr int kMaskWords = kMaxTokens / 64;
-  __shared__ float ell_s[kStaged ? kStage : 1];
+  constexpr int kNJ = (kG * kS + 63) / 64;  // expert slots per lane of TopCap's wave
+  __shared__ __align__(16) float ell_s[kStaged ? kStage : 1];
   __shared__ float w_s[kMaxTokens];
   __shared__ float gap_s[kMaxTokens];
   __shared__ float gm_s[kMaxExperts];                  // g of every expert
@@ -85,10 +108,35 @@ __global__ __launch_bounds__(1024) void reuse_gate_kernel(GateArgs a, RouteArgs 
   const int active = __syncthreads_or(positive);
   const float* ell = kStaged ? static_cast<const float*>(ell_s) : a.logits;
 
+  // Team t of wave w takes tokens kTeams w + t, + kTeams n_waves, ...
+  constexpr int kTeams = kWave / kG;
+  const int team = lane / kG, e0 = (lane % kG) * kS;
   if (kSelect) {
-    for (int b = wave; b < B; b += n_waves)
-      wave_select_plain<kNJ>(E, k, ell + (size_t)b * E, plain_s + b * k, gap_s + b,
-                             ra.plain_idx + (size_t)b * k, ra.gap + b);
+    // Exact top-(k+1) by (value desc, id asc): the last one taken is the
+    // (k+1)-th, the others are the plain top-k.
+    for (int b0 = wave * kTeams; b0 < B; b0 += n_waves * kTeams) {
+      const int b = b0 + team;
+      float l[kS];
+      load_row<kS>(ell + (size_t)min(b, B - 1) * E, e0, E, b < B, l);
+      uint32_t key[kS];
+#pragma unroll
+      for (int s = 0; s < kS; ++s) key[s] = b < B && e0 + s < E ? order_key(l[s]) : 0u;
+      uint32_t bits = 0, rest = 0;
+      const uint32_t first = team_take_max<kG, kS>(key, bits);
+      for (int j = 1; j < k; ++j) team_take_max<kG, kS>(key, bits);
+      const float gv = key_value(first) - key_value(team_take_max<kG, kS>(key, rest));
+      int pos = b * k + team_exclusive_scan<kG>(__popc(bits));
+#pragma unroll
+      for (int s = 0; s < kS; ++s)
+        if ((bits >> s) & 1u) {
+          ra.plain_idx[pos] = e0 + s;
+          plain_s[pos++] = (uint8_t)(e0 + s);
+        }
+      if (b < B && lane % kG == 0) {
+        gap_s[b] = gv;
+        ra.gap[b] = gv;
+      }
+    }
     __syncthreads();
   }
 
@@ -158,70 +206,51 @@ __global__ __launch_bounds__(1024) void reuse_gate_kernel(GateArgs a, RouteArgs 
   __syncthreads();
 
   // Per token: lambda_b, biased keys, biased top-k, gate weights, masks.
-  // Wave w takes tokens w, w + 16, ...; kNT of them at a time.
   const bool from_biased = (a.flags & kGateFromBiased) != 0;
-  for (int b0 = wave; b0 < B; b0 += n_waves * kNT) {
-    float l[kNT][kNJ], lb[kNT][kNJ];
-    uint32_t key[kNT][kNJ];
+  for (int b0 = wave * kTeams; b0 < B; b0 += n_waves * kTeams) {
+    const int b = b0 + team;
+    const bool real = b < B;
+    float lam = 0.f;
+    if (active && real) lam = (a.flags & kBiasAbsolute) ? a.alpha : a.alpha * gap_s[b];
+    float l[kS], x[kS];  // x: what the gate weights are taken from
+    uint32_t key[kS], xkey[kS];
+    load_row<kS>(ell + (size_t)min(b, B - 1) * E, e0, E, real, l);
 #pragma unroll
-    for (int t = 0; t < kNT; ++t) {
-      const int b = b0 + t * n_waves;
-      float lam = 0.f;
-      if (active && b < B) lam = (a.flags & kBiasAbsolute) ? a.alpha : a.alpha * gap_s[b];
-#pragma unroll
-      for (int j = 0; j < kNJ; ++j) {
-        const int e = lane + kWave * j;
-        l[t][j] = 0.f;
-        lb[t][j] = 0.f;
-        key[t][j] = 0;
-        if (b < B && e < E) {
-          l[t][j] = ell[(size_t)b * E + e];
-          lb[t][j] = pref_s[e] ? l[t][j] + lam : l[t][j];
-          key[t][j] = order_key(lb[t][j]);
-        }
-      }
+    for (int s = 0; s < kS; ++s) {
+      const bool in = real && e0 + s < E;
+      const float lb = in && pref_s[e0 + s] ? l[s] + lam : l[s];
+      x[s] = from_biased ? lb : l[s];
+      key[s] = in ? order_key(lb) : 0u;
+      xkey[s] = from_biased ? key[s] : order_key(l[s]);
     }
-    uint32_t bits[kNT];
-    wave_top_k<kNT, kNJ>(key, k, bits);
+    uint32_t bits = 0;
+    for (int j = 0; j < k; ++j) team_take_max<kG, kS>(key, bits);
     // Softmax over the selected k: max through the order keys (exact),
-    // then exp, a DPP sum and one reciprocal.
-    float ez[kNT][kNJ], s[kNT], inv_s[kNT];
+    // then exp, a team sum and one reciprocal.
+    uint32_t mk = 0;
 #pragma unroll
-    for (int t = 0; t < kNT; ++t) {
-      uint32_t mk = 0;
+    for (int s = 0; s < kS; ++s)
+      if ((bits >> s) & 1u) mk = max(mk, xkey[s]);
+    const float m = key_value(team_max_key<kG>(mk));
+    float ez[kS], sum = 0.f;
 #pragma unroll
-      for (int j = 0; j < kNJ; ++j)
-        if ((bits[t] >> j) & 1u) mk = max(mk, from_biased ? key[t][j] : order_key(l[t][j]));
-      const float m = key_value(wave_max_key_dpp(mk));
-      s[t] = 0.f;
-#pragma unroll
-      for (int j = 0; j < kNJ; ++j) {
-        // exp(x - m) as 2^((x - m) log2 e) on the hardware exp2 (about 1e-6
-        // relative error for |x - m| < 20)
-        const float x = from_biased ? lb[t][j] : l[t][j];
-        ez[t][j] = ((bits[t] >> j) & 1u) ? __builtin_amdgcn_exp2f((x - m) * kLog2e) : 0.f;
-        s[t] += ez[t][j];
-      }
+    for (int s = 0; s < kS; ++s) {
+      // exp(x - m) as 2^((x - m) log2 e) on the hardware exp2 (about 1e-6
+      // relative error for |x - m| < 20)
+      ez[s] = ((bits >> s) & 1u) ? __builtin_amdgcn_exp2f((x[s] - m) * kLog2e) : 0.f;
+      sum += ez[s];
     }
+    const float inv_s = __builtin_amdgcn_rcpf(team_sum<kG>(sum));
+    int pos = b * k + team_exclusive_scan<kG>(__popc(bits));
 #pragma unroll
-    for (int t = 0; t < kNT; ++t) inv_s[t] = __builtin_amdgcn_rcpf(wave_sum_dpp(s[t]));
-#pragma unroll
-    for (int t = 0; t < kNT; ++t) {
-      const int b = b0 + t * n_waves;
-      if (b >= B) break;
-      int rank[kNJ];
-      wave_rank_flagged<kNJ>(bits[t], rank);
-#pragma unroll
-      for (int j = 0; j < kNJ; ++j) {
-        if ((bits[t] >> j) & 1u) {
-          const int pos = b * k + rank[j];
-          const int e = lane + kWave * j;
-          a.idx[pos] = e;
-          a.gate_w[pos] = ez[t][j] * inv_s[t];
-          idx_s[pos] = (uint8_t)e;
-          atomicOr(reinterpret_cast<unsigned long long*>(&mask_s[e][b >> 6]),
-                   1ull << (b & 63));
-        }
+    for (int s = 0; s < kS; ++s) {
+      if ((bits >> s) & 1u) {
+        const int e = e0 + s;
+        a.idx[pos] = e;
+        a.gate_w[pos] = ez[s] * inv_s;
+        idx_s[pos] = (uint8_t)e;
+        ++pos;
+        atomicOr(reinterpret_cast<unsigned long long*>(&mask_s[e][b >> 6]), 1ull << (b & 63));
       }
     }
   }
@@ -310,24 +339,28 @@ __global__ __launch_bounds__(kWave) void route_gate_small_kernel(RouteArgs ra, G
   small_route_gate<kNJ>(ra, a, s, true);
 }
 
-template <bool kStaged, int kNJ, bool kSelect>
-void launch_gate_nj(const GateArgs& a, const RouteArgs& ra, hipStream_t s) {
-  if (a.B <= 16)
-    hipLaunchKernelGGL((reuse_gate_kernel<kStaged, kNJ, 1, kSelect>), dim3(1), dim3(1024), 0, s, a, ra);
-  else if (a.B <= 32)
-    hipLaunchKernelGGL((reuse_gate_kernel<kStaged, kNJ, 2, kSelect>), dim3(1), dim3(1024), 0, s, a, ra);
-  else
-    hipLaunchKernelGGL((reuse_gate_kernel<kStaged, kNJ, 4, kSelect>), dim3(1), dim3(1024), 0, s, a, ra);
+template <bool kStaged, bool kSelect, int kG, int kS>
+void launch_gate_team(const GateArgs& a, const RouteArgs& ra, hipStream_t s) {
+  hipLaunchKernelGGL((reuse_gate_kernel<kStaged, kG, kS, kSelect>), dim3(1), dim3(1024), 0, s, a, ra);
 }
+
+// Up to 16 tokens each of the 16 waves has at most one, and a whole wave per
+// token is the shorter chain (16 tokens over 128 experts: the call takes 39.8
+// us against 41.4 with 16-lane rows); above, rows take four tokens a wave (32
+// tokens 93.1 against 94.7 us, 64 tokens 65.9 against 72.8).  16 experts or
+// fewer need one slot a lane either way.
+constexpr int kWaveTeamMaxTokens = 16;
 
 template <bool kStaged, bool kSelect>
 void launch_gate_staged(const GateArgs& a, const RouteArgs& ra, hipStream_t s) {
-  if (a.E <= 64)
-    launch_gate_nj<kStaged, 1, kSelect>(a, ra, s);
-  else if (a.E <= 128)
-    launch_gate_nj<kStaged, 2, kSelect>(a, ra, s);
-  else
-    launch_gate_nj<kStaged, 4, kSelect>(a, ra, s);
+  const bool wide = a.B <= kWaveTeamMaxTokens;
+  if (a.E <= 16) launch_gate_team<kStaged, kSelect, 16, 1>(a, ra, s);
+  else if (a.E <= 64 && wide) launch_gate_team<kStaged, kSelect, 64, 1>(a, ra, s);
+  else if (a.E <= 64) launch_gate_team<kStaged, kSelect, 16, 4>(a, ra, s);
+  else if (a.E <= 128 && wide) launch_gate_team<kStaged, kSelect, 64, 2>(a, ra, s);
+  else if (a.E <= 128) launch_gate_team<kStaged, kSelect, 16, 8>(a, ra, s);
+  else if (wide) launch_gate_team<kStaged, kSelect, 64, 4>(a, ra, s);
+  else launch_gate_team<kStaged, kSelect, 16, 16>(a, ra, s);
 }
 
 bool small_gate_applies(const GateArgs& a) {
@@ -352,21 +385,29 @@ hipError_t launch_reuse_gate(const GateArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// The workgroup gating kernel ranks the tokens itself when each of its 16
-// waves has at most one token to rank (measured on MI355X: 3.6 us saved at
-// 4 tokens, 0.8 us lost at 32, where the routing launch ranks the tokens on
-// 32 compute units at once).
-constexpr int kGateSelectMaxTokens = 16;
+// The workgroup gating kernel ranks the tokens itself, after the logits-only
+// launch, up to this many of them: more would wait for the one workgroup
+// longer than the launch saved.  Measured on MI355X, calls with a ranking of
+// their own against this: 128 experts, where it is a launch, at 32 tokens
+// 94.6 against 92.6 us, but at 64 tokens 65.7 against 66.6; 64 experts, where
+// one workgroup per token also computes the logits, at 12 / 24 / 64 tokens
+// 39.5 / 56.6 / 142 against 37.5 / 54.4 / 140 us, at 100 tokens 81.2 against
+// 82.6.
+constexpr int kGateSelectMaxTokens = 32;
+constexpr int kGateSelectMaxTokens64 = 64;  // up to 64 experts
 
 hipError_t launch_route_and_gate(const RouteArgs& ra, const GateArgs& a, hipStream_t s) {
-  if (!route_ranks_separately(ra) ||
-      (!small_gate_applies(a) && (a.B * a.E > kStage || a.B > kGateSelectMaxTokens))) {
+  const bool small = small_gate_applies(a) && route_ranks_separately(ra);
+  const bool select = (route_ranks_separately(ra) || route_rows_same_bits(ra)) &&
+                      a.B * a.E <= kStage &&
+                      a.B <= (a.E <= 64 ? kGateSelectMaxTokens64 : kGateSelectMaxTokens);
+  if (!small && !select) {
     const hipError_t err = launch_route(ra, s);
     return err != hipSuccess ? err : launch_reuse_gate(a, s);
   }
   const hipError_t err = launch_route_rows(ra, s);
   if (err != hipSuccess) return err;
-  if (small_gate_applies(a)) {
+  if (small) {
     if (a.E <= 64)
       hipLaunchKernelGGL(route_gate_small_kernel<1>, dim3(1), dim3(kWave), 0, s, ra, a);
     else if (a.E <= 128)

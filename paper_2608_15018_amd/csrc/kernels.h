@@ -216,6 +216,10 @@ hipError_t launch_route_rows(const RouteArgs& a, hipStream_t s);
 // Whether launch_route computes the logits and ranks them in two launches
 // (launch_route_rows, then one wave per token).
 bool route_ranks_separately(const RouteArgs& a);
+// Whether launch_route_rows' logits equal launch_route's bit for bit although
+// launch_route ranks in the same launch: H is not sliced there, so both add
+// the same terms in the same order.
+bool route_rows_same_bits(const RouteArgs& a);
 // launch_route then launch_reuse_gate, with the same results bit for bit;
 // where the routing ranks in a launch of its own, the gating launch ranks
 // the logits itself instead (gate.hip).

@@ -154,6 +154,10 @@ bool route_ranks_separately(const RouteArgs& a) {
   return a.B <= S2MOE_ROUTE_ROWS_MAX_B || a.E > S2MOE_ROUTE_ROWS_MIN_E;
 }
 
+bool route_rows_same_bits(const RouteArgs& a) {
+  return route_slices(a.E, a.H / (a.bf16 ? 8 : 4)) == 1;
+}
+
 hipError_t launch_route(const RouteArgs& a, hipStream_t s) {
   if (route_ranks_separately(a)) {
     const hipError_t e = launch_route_rows(a, s);

@@ -135,6 +135,76 @@ __device__ __forceinline__ void wave_top_k(const uint32_t (&key)[NT][NJ], int k,
   }
 }
 
+// ---- a token's keys in a team of G lanes, S per lane: the whole wave (G = 64)
+// or a 16-lane row (G = 16, four tokens per wave).  Slot s of team lane r is
+// expert r S + s; empty slots hold key 0.
+
+// Every lane gets the maximum over its team.
+template <int G>
+__device__ __forceinline__ uint32_t team_max_key(uint32_t x) {
+  if (G == 64) return wave_max_key_dpp(x);
+  int v = (int)x;
+  v = (int)max((uint32_t)v, (uint32_t)S2MOE_DPP(0, v, 0x128, 0xF));  // row_ror:8
+  v = (int)max((uint32_t)v, (uint32_t)S2MOE_DPP(0, v, 0x124, 0xF));  // row_ror:4
+  v = (int)max((uint32_t)v, (uint32_t)S2MOE_DPP(0, v, 0x122, 0xF));  // row_ror:2
+  v = (int)max((uint32_t)v, (uint32_t)S2MOE_DPP(0, v, 0x121, 0xF));  // row_ror:1
+  return (uint32_t)v;
+}
+
+// Every lane gets the sum over its team (in a row, rotations pair the lanes
+// symmetrically, so every lane adds the same values in the same tree).
+template <int G>
+__device__ __forceinline__ float team_sum(float x) {
+  if (G == 64) return wave_sum_dpp(x);
+  int v = __float_as_int(x);
+  v = __float_as_int(__int_as_float(v) + __int_as_float(S2MOE_DPP(0, v, 0x128, 0xF)));
+  v = __float_as_int(__int_as_float(v) + __int_as_float(S2MOE_DPP(0, v, 0x124, 0xF)));
+  v = __float_as_int(__int_as_float(v) + __int_as_float(S2MOE_DPP(0, v, 0x122, 0xF)));
+  v = __float_as_int(__int_as_float(v) + __int_as_float(S2MOE_DPP(0, v, 0x121, 0xF)));
+  return __int_as_float(v);
+}
+
+// Sum over the team's lanes before this one.
+template <int G>
+__device__ __forceinline__ int team_exclusive_scan(int x) {
+  if (G == 64) return wave_inclusive_scan_dpp(x) - x;
+  int v = x;
+  v += S2MOE_DPP(0, v, 0x111, 0xF);  // row_shr:1
+  v += S2MOE_DPP(0, v, 0x112, 0xF);  // row_shr:2
+  v += S2MOE_DPP(0, v, 0x114, 0xF);  // row_shr:4
+  v += S2MOE_DPP(0, v, 0x118, 0xF);  // row_shr:8
+  return v - x;
+}
+
+// Takes the team's largest key (ties: lowest expert id) out of `key`: returns
+// it, and sets its bit in the bits of the lane that held it.  A team without
+// keys left gives 0 and sets nothing.
+template <int G, int S>
+__device__ __forceinline__ uint32_t team_take_max(uint32_t (&key)[S], uint32_t& bits) {
+  uint32_t m = key[0];
+#pragma unroll
+  for (int s = 1; s < S; ++s) m = max(m, key[s]);
+  const uint32_t top = team_max_key<G>(m);
+  const int lane = threadIdx.x & (kWave - 1);
+  const uint64_t holders = __ballot(m == top);  // never empty within a team
+  int first;
+  if (G == 64)
+    first = __builtin_ctzll(holders);
+  else
+    first = (lane & 48) + __builtin_ctz((uint32_t)(holders >> (lane & 48)) | 0x10000u);
+  bool open = top != 0u && lane == first;  // the lane's first slot with the key
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    const bool hit = open && key[s] == top;
+    if (hit) {
+      key[s] = 0u;
+      bits |= 1u << s;
+    }
+    open = open && !hit;
+  }
+  return top;
+}
+
 // Rank, in ascending expert id, of the flagged experts: expert lane + 64 j
 // with bit j set gets position rank[j].  Returns the number flagged.
 template <int NJ>

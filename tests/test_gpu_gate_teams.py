@@ -1,0 +1,63 @@
+"""The gating kernel's per-token ranking by teams of lanes (a wave, or a row of
+16 lanes) against the fp64 oracle on dyadic logits with many exact ties, and
+the one-call layer's ranking inside the gating launch against the four calls."""
+
+import numpy as np
+import pytest
+
+import oracle
+from synth.configs import LayerShape
+from tests.gpu_helpers import assert_same_bits, check_routing, log, make_inputs, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+# Expert counts at the edges of a team's slots (1, 4, 8, 16 a row lane; 1, 2, 4
+# a wave lane) and not multiples of 4; token counts at the edges of a wave per
+# token (16), of a row group (4) and of a workgroup pass (64).
+@pytest.mark.parametrize("E,k,cap", [(2, 1, 1), (3, 2, 2), (16, 15, 16), (17, 16, 17), (63, 6, 9),
+                                     (64, 8, 16), (66, 3, 40), (127, 16, 20), (128, 8, 14),
+                                     (129, 5, 7), (255, 16, 30), (256, 12, 100)])
+def test_ties_over_team_edges(E, k, cap):
+    import paper_2608_15018_amd as s2
+    rng = np.random.default_rng(E * 31 + k)
+    H = -(-E // 64) * 64
+    router = np.zeros((E, H), np.float32)
+    router[np.arange(E), np.arange(E)] = 1.0
+    for B in (1, 3, 5, 16, 17, 63, 65, 256):
+        # eighths in [-2, 2]: with alpha 0.5 every g, bias and biased logit is exact
+        x = np.zeros((B, H), np.float32)
+        x[:, :E] = rng.integers(-16, 17, size=(B, E)) / 8.0
+        w = (rng.random(B) < 0.7).astype(np.float32)
+        w[0] = 1.0
+        log(f"[gate] E={E} k={k} cap={cap} B={B}")
+        r = oracle.route(x, router, k, "f32")
+        for flags in (0, 1, 2 | 4):
+            ref = oracle.reuse_gate(r["logits"], r["gap"], r["plain_idx"], w, k, cap, 0.5, flags)
+            L = s2.make_layer(hidden=H, ffn=64, n_experts=E, top_k=k, cap=cap, alpha=0.5,
+                              flags=flags, act="f32", wdt="f32")
+            rt = s2.Routing(L, B)
+            s2.route(L, torch.from_numpy(x).cuda(), torch.from_numpy(router).cuda(), rt)
+            s2.reuse_gate(L, torch.from_numpy(w).cuda(), rt)
+            torch.cuda.synchronize()
+            got, label = rt.host(), f"E={E} B={B} flags={flags}"
+            for n in ("pref", "idx", "count", "offset", "slot", "uniq"):
+                np.testing.assert_array_equal(got[n], ref[n], err_msg=f"{n} {label}")
+            # k terms of at most 1, each within 1e-6, and their sum's rounding
+            assert np.abs(got["gate_w"] - ref["gate_w"]).max() <= 5e-6, label
+
+
+@pytest.mark.parametrize("E,k,B", [(40, 4, 9), (64, 6, 33), (64, 6, 64), (64, 6, 65), (36, 3, 24),
+                                   (100, 8, 17), (128, 8, 32), (128, 8, 33), (32, 4, 24)])
+def test_ranking_inside_the_gating_launch(E, k, B):
+    shape = LayerShape(hidden=256, ffn=64, n_experts=E, top_k=k, cap=2 * k, alpha=0.5)
+    d = make_inputs(shape, B, seed=E + B, rho=0.5)
+    label = f"E={E} k={k} B={B}"
+    log(f"[gate] one call {label}")
+    four, dw = run_gpu(shape, d)
+    one, _ = run_gpu(shape, d, dw, fused=True)
+    assert_same_bits(one, four, label)
+    ref = oracle.forward(d["x"], d["router"], d["conf_w"], d["experts"], d["shared"], shape)
+    check_routing(one, ref, label)
