@@ -52,8 +52,13 @@
 //   (D = 2: the decode, not the memory latency, bounds the stream; deeper
 //   rings of 3, 4, 6 and 8 were 2-35 % slower on MI355X as their registers
 //   cost occupancy).
-// - Up to TMAX = 4 token tiles (64 tokens) share one pass over the weights;
-//   larger buckets take further passes.
+// - Up to TMAX = 4 token tiles (64 tokens; 8 above 128 tokens in the batch)
+//   share one pass over the weights; larger buckets take further passes.
+//   Eight tiles halve the decoding of a bucket of more than 64 tokens, but
+//   their registers leave two waves per SIMD instead of three: Mixtral-shaped
+//   layers at 80 / 128 / 180 / 256 tokens 171 / 216 / 328 / 404 us with four,
+//   185 / 216 / 279 / 381 with eight; 64 experts of F = 1024 at 200 tokens
+//   124 -> 115 us.
 // - Gate-up items span all of K (Q = 1), so SwiGLU is applied in the
 //   epilogue.  Down items split K into Q parts when few experts are active:
 //   part 0 writes expert_out, parts 1..Q-1 write partial sums to the
@@ -640,7 +645,11 @@ __global__ __launch_bounds__(kW * 64, TMAX >= 4 ? S2MOE_Q4_MINWAVES_T4 : 1) void
     const uint16_t* S1 = static_cast<const uint16_t*>(Q1) + seg.id * (mat / 32);
     for (int t0 = 0; t0 < seg.n; t0 += 16 * TMAX) {
       const int T = min(TMAX, (seg.n - t0 + 15) / 16);
-      if (TMAX >= 4 && T >= 4)
+      if (TMAX >= 8 && T >= 7)
+        q4_pass<kMode, (TMAX >= 8 ? 8 : 1), R, D, A, C, kPacked>(a, seg, t0, r0, q, lo, hi, K, C0, C1, S0, S1, lds);
+      else if (TMAX >= 8 && T >= 5)
+        q4_pass<kMode, (TMAX >= 8 ? 6 : 1), R, D, A, C, kPacked>(a, seg, t0, r0, q, lo, hi, K, C0, C1, S0, S1, lds);
+      else if (TMAX >= 4 && T >= 4)
         q4_pass<kMode, (TMAX >= 4 ? 4 : 1), R, D, A, C, kPacked>(a, seg, t0, r0, q, lo, hi, K, C0, C1, S0, S1, lds);
       else if (TMAX >= 3 && T == 3)
         q4_pass<kMode, (TMAX >= 3 ? 3 : 1), R, D, A, C, kPacked>(a, seg, t0, r0, q, lo, hi, K, C0, C1, S0, S1, lds);
@@ -917,9 +926,6 @@ hipError_t launch_q4_layout(const FfnArgs& a, int Q, hipStream_t s) {
 #ifndef S2MOE_Q4_CHUNK
 #define S2MOE_Q4_CHUNK 1
 #endif
-#ifndef S2MOE_Q4_TMAX_LARGE
-#define S2MOE_Q4_TMAX_LARGE 4
-#endif
 #ifndef S2MOE_Q4_GATEUP_R
 #define S2MOE_Q4_GATEUP_R 1
 #endif
@@ -1075,7 +1081,8 @@ hipError_t launch_ffn_q4(const FfnArgs& a, hipStream_t s) {
   // Token tiles held in one pass: the batch bounds every bucket.
   if (a.B <= 16) err = launch_q4_pair<1>(a, s);
   else if (a.B <= 32) err = launch_q4_pair<2>(a, s);
-  else err = launch_q4_pair<S2MOE_Q4_TMAX_LARGE>(a, s);
+  else if (a.B <= 128) err = launch_q4_pair<4>(a, s);
+  else err = launch_q4_pair<8>(a, s);
   if (err != hipSuccess || a.qparts <= 1 || a.defer_reduce) return err;
   const size_t n4 = ((size_t)a.B * a.k + (size_t)a.S * a.B) * a.H / 4;
   const dim3 grid((unsigned)((n4 + 255) / 256));
