@@ -58,46 +58,72 @@ __device__ __forceinline__ void wave_sync() {
 // member (smallest value, then largest id) is the (k+1)-th, the other k are
 // the plain top-k, written in id order to idx[0..k); gap = ell_(1) -
 // ell_(k+1) to *gap.  idx2 / gap2, when not null, get the same values.
+// Below kTakeMaxK experts the largest key is taken k + 1 times (a DPP chain
+// each); more of them cost more than the threshold search's 16 ballot steps.
+// Draft steps on MI355X, by the search and by taking maxima: Qwen3-shaped, 3
+// experts, 1 / 4 tokens 857 / 1627 -> 832 / 1522 us; GPT-OSS-shaped, 2 tokens
+// 1079 -> 1026; OLMoE-shaped int4, 3 tokens 335 -> 321 us.
+constexpr int kTakeMaxK = 12;
+
 template <int NJ, class I1, class I2>
 __device__ __forceinline__ void wave_select_plain(int E, int k, const float* ell, I1* idx,
                                                   float* gap, I2* idx2, float* gap2) {
   const int lane = threadIdx.x & (kWave - 1);
-  uint32_t key[1][NJ];
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    const int e = lane + kWave * j;
-    key[0][j] = e < E ? order_key(ell[e]) : 0u;
-  }
-  uint32_t sel[1];
-  wave_top_k<1, NJ>(key, k + 1, sel);
-  uint32_t mn = 0xFFFFFFFFu, mx = 0u;
-#pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    if ((sel[0] >> j) & 1u) mn = min(mn, key[0][j]);
-    mx = max(mx, key[0][j]);
-  }
-  mn = ~wave_max_key_dpp(~mn);
-  mx = wave_max_key_dpp(mx);
-  int last = -1;
-#pragma unroll
-  for (int j = NJ - 1; j >= 0; --j) {
-    const uint64_t m = __ballot(((sel[0] >> j) & 1u) && key[0][j] == mn);
-    if (last < 0 && m) last = kWave * j + 63 - __builtin_clzll(m);
-  }
-  uint32_t bits = 0;
-#pragma unroll
-  for (int j = 0; j < NJ; ++j)
-    if (((sel[0] >> j) & 1u) && lane + kWave * j != last) bits |= 1u << j;
+  uint32_t bits = 0, top, low;
   int rank[NJ];
-  wave_rank_flagged<NJ>(bits, rank);
+  if (k < kTakeMaxK) {
+    uint32_t key[NJ], rest = 0;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int e = lane * NJ + j;
+      key[j] = e < E ? order_key(ell[e]) : 0u;
+    }
+    top = team_take_max<64, NJ>(key, bits);
+    for (int q = 1; q < k; ++q) team_take_max<64, NJ>(key, bits);
+    low = team_take_max<64, NJ>(key, rest);
+    int pos = team_exclusive_scan<64>(__popc(bits));
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      rank[j] = pos;
+      pos += (bits >> j) & 1u;
+    }
+  } else {
+    uint32_t key[1][NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int e = lane + kWave * j;
+      key[0][j] = e < E ? order_key(ell[e]) : 0u;
+    }
+    uint32_t sel[1];
+    wave_top_k<1, NJ>(key, k + 1, sel);
+    uint32_t mn = 0xFFFFFFFFu, mx = 0u;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      if ((sel[0] >> j) & 1u) mn = min(mn, key[0][j]);
+      mx = max(mx, key[0][j]);
+    }
+    low = ~wave_max_key_dpp(~mn);
+    top = wave_max_key_dpp(mx);
+    int last = -1;
+#pragma unroll
+    for (int j = NJ - 1; j >= 0; --j) {
+      const uint64_t m = __ballot(((sel[0] >> j) & 1u) && key[0][j] == low);
+      if (last < 0 && m) last = kWave * j + 63 - __builtin_clzll(m);
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+      if (((sel[0] >> j) & 1u) && lane + kWave * j != last) bits |= 1u << j;
+    wave_rank_flagged<NJ>(bits, rank);
+  }
+  const int e0 = k < kTakeMaxK ? lane * NJ : lane, de = k < kTakeMaxK ? 1 : kWave;
 #pragma unroll
   for (int j = 0; j < NJ; ++j)
     if ((bits >> j) & 1u) {
-      idx[rank[j]] = (I1)(lane + kWave * j);
-      if (idx2) idx2[rank[j]] = (I2)(lane + kWave * j);
+      idx[rank[j]] = (I1)(e0 + j * de);
+      if (idx2) idx2[rank[j]] = (I2)(e0 + j * de);
     }
   if (lane == 0) {
-    const float gv = key_value(mx) - key_value(mn);
+    const float gv = key_value(top) - key_value(low);
     *gap = gv;
     if (gap2) *gap2 = gv;
   }
