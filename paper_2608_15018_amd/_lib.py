@@ -169,6 +169,10 @@ def _ptr(t) -> int | None:
 
 def _stream(stream) -> int:
     if stream is None:
+        # torch.cuda.current_stream() builds a Stream object: 2.6 us of a
+        # call's 17 at the smallest layer.
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
