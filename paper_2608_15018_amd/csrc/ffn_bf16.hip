@@ -2,15 +2,20 @@
 //
 // Unit of work: R consecutive 16-row tiles of one expert matrix pair (gate
 // and up) or one down matrix, for all tokens routed to that expert.  The W
-// waves of the workgroup split the reduction dimension K, dealt in runs of
-// two or more steps so that the waves read consecutive kilobytes of a row
-// tile at a time; each wave streams its share with a double-buffered register
-// pipeline (the next chunk of steps is in flight while the current one
-// feeds the MFMAs), and the W partial tiles are added through LDS in wave
-// order, so results do not depend on timing.  Dealt runs against one
-// contiguous range per wave, step times on MI355X: H = 4096, F = 14336 at
-// 6 / 16 / 32 / 64 tokens 275 / 350 / 430 / 441 -> 269 / 348 / 391 / 432 us,
-// row-major H = F = 2880 at 10 / 20 tokens 181 / 299 -> 170 / 285 us.
+// waves of the workgroup split the reduction dimension K; each wave streams its
+// share with a double-buffered register pipeline (the next chunk of steps is
+// in flight while the current one feeds the MFMAs), and the W partial tiles
+// are added through LDS in wave order, so results do not depend on timing.
+//
+// A wave's share of K is one contiguous range or, above 16 tokens, runs of two
+// steps dealt to the waves (k_share), which read consecutive kilobytes of a
+// packed row tile at a time.  Step times on MI355X, ranges against runs:
+// packed, H = 4096, F = 14336 at 24 / 32 tokens 482 / 428 -> 433 / 389 us;
+// row-major, H = F = 2880 at 24 tokens 316 -> 300 us, but with rows a multiple
+// of 4 KB, which runs read from a few L2 channels at a time, H = 4096 24
+// tokens 487 -> 554 us and 32 tokens over 256 experts of H = 2048, F = 512
+// 137 -> 147 us.  Up to 16 tokens runs gained packed weights 1-3 % and cost
+// row-major ones of H = 2048 up to 10 % (OLMoE-shaped, 4 tokens 69.5 -> 76.8).
 //
 // Per 32-wide K step a lane loads 16 bytes of each of its R weight rows (the
 // A operand of v_mfma_f32_16x16x32_bf16: row = lane % 16, K slice =
@@ -74,6 +79,32 @@ __device__ __forceinline__ void compute_stage(const Stage<T, R, NM, U>& st,
   }
 }
 
+// A wave's share of the nks steps of K: stage c is the steps from step(c), U
+// of them or as many as are below `end`.
+template <int U>
+struct KShare {
+  static constexpr int kRun = U >= 2 ? 1 : 2;  // stages per run of two steps
+  int first, stride, end, stages;
+  bool runs;
+  __device__ __forceinline__ int step(int c) const {
+    return first + (kRun == 1 || !runs ? c * stride : c / kRun * stride + c % kRun * U);
+  }
+};
+
+// Runs dealt to the waves (kRuns, where `runs` agrees), else a contiguous
+// range.
+template <int U, int W, bool kRuns>
+__device__ __forceinline__ KShare<U> k_share(int wave, int nks, bool runs) {
+  constexpr int kRun = KShare<U>::kRun;
+  if (kRuns && runs) {
+    const int all = (nks + U - 1) / U, rounds = all / (kRun * W);
+    const int left = all - rounds * kRun * W - wave * kRun;
+    return {wave * kRun * U, W * kRun * U, nks, rounds * kRun + min(max(left, 0), kRun), true};
+  }
+  const int lo = wave * nks / W, hi = (wave + 1) * nks / W;
+  return {lo, U, hi, (hi - lo + U - 1) / U, false};
+}
+
 // One pass over up to 16*T tokens of the unit, all of the wave's K range.
 template <int kMode, int T, int TMAX, int R, int W, int U, bool kPacked>
 __device__ __forceinline__ void unit_pass(const FfnArgs& a, const Segment& seg, int t0, int r0,
@@ -114,16 +145,12 @@ __device__ __forceinline__ void unit_pass(const FfnArgs& a, const Segment& seg, 
     for (int r = 0; r < R; ++r)
 #pragma unroll
       for (int tt = 0; tt < T; ++tt) acc[m][r][tt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // Stage c of the wave: K is dealt to the waves in runs of at least two steps.
-  constexpr int kRun = U >= 2 ? 1 : 2;  // stages per run
-  auto step_of = [&](int c) { return ((c / kRun * W + wave) * kRun + c % kRun) * U; };
-  const int n_stages = (nks + U - 1) / U, rounds = n_stages / (kRun * W);
-  const int left = n_stages - rounds * kRun * W - wave * kRun;
-  const int n = rounds * kRun + min(max(left, 0), kRun);
-  if (n > 0) {
+  const KShare<U> ks = k_share<U, W, (TMAX > 1)>(wave, nks, kPacked || TMAX > 2 || K % 2048 != 0);
+  if (ks.stages > 0) {
     pipeline2<Stage<T, R, NM, U>>(
-        n, [&](Stage<T, R, NM, U>& st, int c) { load_stage<kPacked>(st, pa, xb, step_of(c), nks); },
-        [&](const Stage<T, R, NM, U>& st, int c) { compute_stage(st, acc, step_of(c), nks); });
+        ks.stages,
+        [&](Stage<T, R, NM, U>& st, int c) { load_stage<kPacked>(st, pa, xb, ks.step(c), ks.end); },
+        [&](const Stage<T, R, NM, U>& st, int c) { compute_stage(st, acc, ks.step(c), ks.end); });
   }
 
   if (W > 1) {
@@ -285,12 +312,12 @@ __global__ __launch_bounds__(1024) void ffn_bf16_down_combine_kernel(FfnArgs a,
       else
         pa[r] = reinterpret_cast<const u32x4*>(W0 + (size_t)(r0 + 16 * r + rA) * K) + gK;
     }
-    const int first = part * U;
-    if (nks > first) {
+    const KShare<U> ks = k_share<U, KW, false>(part, nks, false);
+    if (ks.stages > 0) {
       pipeline2<Stage<1, R, 1, U>>(
-          (nks - first + KW * U - 1) / (KW * U),
-          [&](Stage<1, R, 1, U>& st, int c) { load_stage<kPacked>(st, pa, xb, first + c * KW * U, nks); },
-          [&](const Stage<1, R, 1, U>& st, int c) { compute_stage(st, acc, first + c * KW * U, nks); });
+          ks.stages,
+          [&](Stage<1, R, 1, U>& st, int c) { load_stage<kPacked>(st, pa, xb, ks.step(c), ks.end); },
+          [&](const Stage<1, R, 1, U>& st, int c) { compute_stage(st, acc, ks.step(c), ks.end); });
     }
   }
   small_down_finish<R, KW>(a, seg, live, part, members, acc, lds, y, r0);
@@ -355,6 +382,7 @@ hipError_t launch_mode(const FfnArgs& a, int spw, hipStream_t s) {
 #ifndef S2MOE_BF16_MEDIUM
 #define S2MOE_BF16_MEDIUM 2, 2, 2, 2, 2, 32, 4
 #endif
+
 #ifndef S2MOE_BF16_LARGE
 #define S2MOE_BF16_LARGE 4, 2, 1, 4, 1, 1
 #endif
@@ -443,9 +471,9 @@ hipError_t launch_moe_layer_small_bf16(const RouteArgs& ra, const GateArgs& ga,
 // 131 / 176 against 134 / 166 us.  Row-major weights, where 32-row units read
 // 128 bytes of a row at a time: 37 tokens at H = F = 2880, 128 experts 395
 // against 351 us, 48 tokens at F = 1024, 64 experts 142 against 137 us, but
-// 24 tokens at F = 768 105 against 107 us.  Up to kWideMinPacked both layouts
-// add the same two K parts in the same order, so their results stay equal
-// bit for bit.
+// 24 tokens at F = 768 105 against 107 us.  From 33 tokens to kWideMinPacked
+// both layouts add the same two K parts in the same order, so their results
+// are equal bit for bit (as up to 16; between, k_share).
 constexpr int kWideMinPacked = 96;
 constexpr int kWideMinRows = 32;
 
