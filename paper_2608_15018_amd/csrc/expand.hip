@@ -7,50 +7,60 @@
 // can never be selected: only the others ("viable", in index order: slots)
 // take part, and only their ids are read.  In LDS, E rounded up to a power of
 // two >= 32 is EW words:
-//   pv[i]            p_i (0 for nodes that are not viable);  cdr[i] = C_i^draft
+//   pv[i]            p_i (0 for nodes that are not viable), later pv[slot] =
+//                    p T_AR;  cdr[slot] = C^draft
 //   rows[slot][l][w] the experts the slot's node is predicted to use at layer l
-//   uni[wave][l][w]  the union U of the selected tokens' (layer, expert) pairs,
-//                    a copy per wave
+//   uni[l][w]        the union U of the selected tokens' (layer, expert) pairs,
+//                    a copy per wave or one for all
 // so that repeated ids collapse by themselves, |E_i \ U| is
 // sum_l popcount(rows[i][l] & ~uni[l]) and U grows by a word-wise OR.
 // Phases: (1) per-node validity and the root's experts into U; (2) prefix
 // confidences and viability; (3) slots; (4) the slots' ids -> bitsets; (5) the
-// greedy loop: each wave lists the candidates from its own flags, each 16-lane
-// row of each wave scores one candidate at a time, the block takes the
-// largest U_i (ties: smaller index) and, if U_i >= 1, every wave adds the
-// node's experts to its copy of U.  A step has one workgroup barrier.
+// greedy loop: each wave lists and scores the candidates among its own slots
+// (those v with v % 4 = wave, so that siblings spread over the waves), each
+// 16-lane row of it one at a time; the block takes the largest U_i (ties:
+// smaller index) and, if U_i >= 1, adds the node's experts to U.  With a copy
+// of U per wave a step has one workgroup barrier, with a single U two.
 //
 // What bounds it is each tree's chain of dependent steps, not bytes, so with
 // more trees than compute units several workgroups share a unit
-// (launch_expand); slots beyond the bitsets in LDS are counted from their ids
-// in memory.  Measured on MI355X against all nodes' ids and bitsets, a
-// candidate list and three barriers per step: one OLMoE-shaped tree
-// 24.0 -> 17.2 us, one Qwen3-shaped tree 20.5 -> 13.5, 400 of them 66 -> 23,
-// 1024 120 -> 26 us; 1024 OLMoE-shaped trees 71 -> 26, GPT-OSS-shaped
-// 73 -> 30 us.
+// (launch_expand).  Measured on MI355X, one launch that reads all nodes' ids,
+// keeps one U and rebuilds a candidate list between three barriers a step,
+// against this: one OLMoE-shaped tree 24.1 -> 15.9 us, one Qwen3-shaped tree
+// 18.9 -> 11.3, 300 of them 61 -> 21, 1024 118 -> 27 us; at T_AR = 100000 (57 to
+// 68 selections a tree) 124 -> 102, 440 -> 440 and 820 -> 712 us.  Trees that
+// fill the LDS, every node selected: 8 nodes at L = 128, E = 1024, k = 32
+// 54 -> 45 us, 104 at L = 48, E = 256 220 -> 195, 1024 at L = 35, E = 32
+// 5.8 -> 5.8 ms; where every node is viable and none is selected the ids are
+// read for nothing after the confidences instead of beside them: 16.6 -> 18.9
+// us for the first of these shapes, 16.0 -> 16.6 for the second.
 #include "common.h"
 #include "kernels.h"
 
 namespace s2moe {
 namespace {
 
-// Which trees a launch takes: all; those whose viable nodes fit its bitsets
-// (the others get n_admit = kLeft); those left.
-enum : int { kAllTrees = 0, kFitting = 1, kRest = 2 };
-constexpr int kLeft = -1;
+constexpr int kLeft = -1;  // n_admit of a tree that a launch leaves to the next one
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
 static_assert(kWaves == kExpandWaves, "copies of the union in LDS");
 
+// A wave's best candidate of a step: U_i and (slot << kNewBits | |E_i \ U|).
+constexpr int kNewBits = 18;  // L E <= 128 * 1024 pairs
+constexpr uint32_t kNone = ~0u;
+
 struct Misc {
-  double red_u[2][kWaves];  // per step parity and wave: the wave's best candidate
-  int red_i[2][kWaves];
-  int red_n[2][kWaves];
-  int viable[4 * kWaves];  // viable nodes per (256-node block, wave)
+  union {
+    int viable[4 * kWaves];  // viable nodes per (256-node block, wave)
+    struct {
+      double u[2][kWaves];  // per step parity and wave
+      uint32_t sn[2][kWaves];
+    } best;
+  };
   int status;
 };
-static_assert(sizeof(Misc) <= 256, "Misc must fit its LDS slot");
+static_assert(sizeof(Misc) <= 112, "Misc must fit its LDS slot");
 
 // U_i from the node's benefit, current new-pair count and C^draft, in the
 // order B / (n * T_exp + c) with no fused multiply-add.
@@ -60,9 +70,9 @@ __device__ __forceinline__ double utility(double ben, int n_new, double t_exp, d
   return ben / cost;
 }
 
-// (u, i) beats (bu, bi): larger utility, then smaller node index.
-__device__ __forceinline__ bool better(double u, int i, double bu, int bi) {
-  return u > bu || (u == bu && i < bi);
+// (u, sn) beats (bu, bsn): larger utility, then smaller slot (= node index).
+__device__ __forceinline__ bool better(double u, uint32_t sn, double bu, uint32_t bsn) {
+  return u > bu || (u == bu && sn < bsn);
 }
 
 __device__ __forceinline__ int wave_sum_int(int v) {
@@ -110,18 +120,18 @@ __device__ __forceinline__ int count_new(const uint32_t* a, const uint32_t* b) {
   return c;
 }
 
-// The same count from the layer's k ids (a slot without a bitset): ids
-// outside [0, E) are padding, repeats count once.
-__device__ __forceinline__ int count_new_ids(const int32_t* e, int k, int E, const uint32_t* u) {
-  int c = 0;
-  for (int x = 0; x < k; ++x) {
-    const int ex = e[x];
-    if ((uint32_t)ex >= (uint32_t)E || ((u[ex >> 5] >> (ex & 31)) & 1u)) continue;
-    bool first = true;
-    for (int y = 0; y < x; ++y) first = first && e[y] != ex;
-    c += first;
+// dst |= src (or dst = src) over W words, by `step` threads of which this is
+// number `at`.
+template <bool kAssign>
+__device__ __forceinline__ void or_words(uint32_t* dst, const uint32_t* src, int W, int at,
+                                         int step) {
+  if ((W & 3) == 0) {  // then every bitset is 16-byte aligned
+    u32x4* d = reinterpret_cast<u32x4*>(dst);
+    const u32x4* s = reinterpret_cast<const u32x4*>(src);
+    for (int w = at; w < (W >> 2); w += step) d[w] = kAssign ? s[w] : (d[w] | s[w]);
+  } else {
+    for (int w = at; w < W; w += step) dst[w] = kAssign ? src[w] : (dst[w] | src[w]);
   }
-  return c;
 }
 
 // Orders a wave's LDS accesses before and after it (each wave works on its own
@@ -142,29 +152,27 @@ __device__ __forceinline__ void lds_store(double* p, double v) {
 }
 
 template <int NPT, int EW>
-__global__ __launch_bounds__(kThreads) void expand_kernel(ExpandArgs a) {
-  extern __shared__ __align__(16) unsigned char lds[];
-  constexpr int Q = NPT * kWaves;  // slots per lane
-  const ExpandLds lay = expand_lds(a.N, a.L, a.E, a.cap);
-  double* pv = reinterpret_cast<double*>(lds + lay.pv);
+__device__ __forceinline__ void expand_tree(const ExpandArgs& a, unsigned char* lds, int t) {
+  const ExpandLds lay = expand_lds(a.N, a.L, a.E, a.cap, a.copies);
+  Misc* misc = reinterpret_cast<Misc*>(lds + lay.misc);
   uint32_t* rows = reinterpret_cast<uint32_t*>(lds + lay.rows);
   uint32_t* uni0 = reinterpret_cast<uint32_t*>(lds + lay.uni);
+  double* pv = reinterpret_cast<double*>(lds + lay.pv);
   float* cdr = reinterpret_cast<float*>(lds + lay.cdr);
   uint16_t* node_of = reinterpret_cast<uint16_t*>(lds + lay.node);
-  uint16_t* slot_of = reinterpret_cast<uint16_t*>(lds + lay.slot);
-  int16_t* par_of = reinterpret_cast<int16_t*>(lds + lay.par);
-  Misc* misc = reinterpret_cast<Misc*>(lds + lay.misc);
+  uint16_t* slot_of = reinterpret_cast<uint16_t*>(pv);  // between phases 2 and 4
+  int16_t* par_of = reinterpret_cast<int16_t*>(lds + lay.list);  // before phase 5
 
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int wave = wave_id();
+  const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
   const int L = a.L, E = a.E, k = a.k, N = a.N;
   const int Lk = L * k, W = L * EW;  // ids and bitset words of a node
-  uint16_t* list = reinterpret_cast<uint16_t*>(lds + lay.list) + wave * N;
-  uint32_t* uni = uni0 + wave * W;
-
-  const int t = blockIdx.x;
-  if (a.pass == kRest && a.n_admit[t] != kLeft) return;
+  const bool copies = a.copies > 1;
+  uint16_t* list =
+      reinterpret_cast<uint16_t*>(lds + lay.list) + wave * ((N + kWaves - 1) / kWaves);
+  uint32_t* uni = uni0 + (copies ? wave * W : 0);
   const size_t node0 = (size_t)t * N;
 
   // (1) per-node records (also the padding's, so that they need not wait for
@@ -198,7 +206,6 @@ __global__ __launch_bounds__(kThreads) void expand_kernel(ExpandArgs a) {
       if (!(par[m] == -1 || (par[m] >= 0 && par[m] < i))) { ok = false; status |= 1; }
       if (!(qd[m] >= 0.f && qd[m] <= 1.f)) { ok = false; status |= 2; }
       if (!(cd[m] > 0.f && cd[m] < INFINITY)) { ok = false; status |= 4; }
-      cdr[i] = cd[m];
       pv[i] = ok ? -1.0 : 0.0;  // -1: not resolved yet
       if (ok) pending |= 1u << m;
     }
@@ -216,11 +223,14 @@ __global__ __launch_bounds__(kThreads) void expand_kernel(ExpandArgs a) {
   }
 
   // (2) prefix confidences, root-down: p_i = p_parent * q_i.  Each wave
-  // re-reads its nodes' parents until all are resolved; a parent has a
-  // smaller index, so the wave that holds it never waits for this one and
-  // every wait ends.  A node whose utility is below 1 even with every expert
-  // in U, or whose parent is such a node or invalid, can never be selected:
-  // its p becomes 0, which makes its children's 0 as well.
+  // re-reads its nodes' parents until all are resolved.  A parent has a
+  // smaller index, so the unresolved node of smallest index always has a
+  // resolved parent (or none), whichever wave holds it: some wave gets on
+  // with every reading, and every wait ends.  A node whose utility is below 1
+  // even with every expert in U, or whose parent is such a node or invalid,
+  // can never be selected: its p becomes 0, which makes its children's 0 as
+  // well.
+  double ben[NPT];
   while (__ballot(pending != 0)) {
 #pragma unroll
     for (int m = 0; m < NPT; ++m) {
@@ -228,7 +238,8 @@ __global__ __launch_bounds__(kThreads) void expand_kernel(ExpandArgs a) {
         const double pp = par[m] < 0 ? 1.0 : lds_load(pv + par[m]);
         if (pp >= 0.0) {
           const double p = pp * (double)qd[m];
-          const bool v = utility(p * a.t_ar, 0, a.t_exp, (double)cd[m]) >= 1.0;
+          ben[m] = p * a.t_ar;
+          const bool v = utility(ben[m], 0, a.t_exp, (double)cd[m]) >= 1.0;
           lds_store(pv + tid + m * kThreads, v ? p : 0.0);
           pending &= ~(1u << m);
           if (v) viable |= 1u << m;
@@ -245,6 +256,7 @@ __global__ __launch_bounds__(kThreads) void expand_kernel(ExpandArgs a) {
   }
   __syncthreads();
   int nv = 0;
+  int slot[NPT];
 #pragma unroll
   for (int m = 0; m < NPT; ++m) {
     int base = nv;
@@ -254,30 +266,32 @@ __global__ __launch_bounds__(kThreads) void expand_kernel(ExpandArgs a) {
       if (w < wave) base += c;
       nv += c;
     }
-    const uint64_t mask = __ballot((viable >> m) & 1u);
-    if ((viable >> m) & 1u) {
-      const int i = tid + m * kThreads;
-      const int v = base + __popcll(mask & (lane == 0 ? 0ull : (~0ull >> (64 - lane))));
-      node_of[v] = (uint16_t)i;
-      slot_of[i] = (uint16_t)v;
-      par_of[v] = (int16_t)par[m];
-    }
+    slot[m] = base + __popcll(__ballot((viable >> m) & 1u) & below);
   }
-  if (a.pass == kFitting && nv > a.cap) {  // left to the launch that follows
+  if (a.leave && nv > a.cap) {  // for the launch that follows
     if (tid == 0) a.n_admit[t] = kLeft;
     return;
   }
-  const int nr = min(nv, a.cap);  // slots with a bitset in LDS
+#pragma unroll
+  for (int m = 0; m < NPT; ++m)
+    if ((viable >> m) & 1u) {
+      node_of[slot[m]] = (uint16_t)(tid + m * kThreads);
+      slot_of[tid + m * kThreads] = (uint16_t)slot[m];
+    }
   {
-    const int words = nr * W;
+    const int words = nv * W;
     u32x4* r4 = reinterpret_cast<u32x4*>(rows);
     for (int w = tid; w < (words >> 2); w += kThreads) r4[w] = u32x4{0u, 0u, 0u, 0u};
     for (int w = (words & ~3) + tid; w < words; w += kThreads) rows[w] = 0u;
   }
   __syncthreads();
+  // The parent of a viable node is viable.
+#pragma unroll
+  for (int m = 0; m < NPT; ++m)
+    if ((viable >> m) & 1u) par_of[slot[m]] = par[m] < 0 ? -1 : (int16_t)slot_of[par[m]];
 
-  // (4) the ids of those slots' nodes -> bitsets; ids outside [0, E) are
-  // padding (they OR 0 into word 0: no branch).
+  // (4) the viable nodes' ids -> bitsets; ids outside [0, E) are padding
+  // (they OR 0 into word 0: no branch).
   const int32_t* ids = a.eid + node0 * (size_t)Lk;
   auto set_bit = [&](uint32_t row, int e) {
     const bool ok = (uint32_t)e < (uint32_t)E;
@@ -285,7 +299,7 @@ __global__ __launch_bounds__(kThreads) void expand_kernel(ExpandArgs a) {
     atomicOr(&rows[w], ok ? 1u << (e & 31) : 0u);
   };
   const int cpn = (Lk + 3) >> 2;  // 4-id chunks of a node
-  const int n_chunks = nr * cpn;
+  const int n_chunks = nv * cpn;
   auto slot_of_chunk = [&](uint32_t c) { return (uint32_t)(((uint64_t)c * a.cpn_div) >> 42); };
   if ((Lk & 3) == 0) {
     // Chunks are 16-byte aligned (eid is); with k a multiple of 4 the four
@@ -334,135 +348,119 @@ __global__ __launch_bounds__(kThreads) void expand_kernel(ExpandArgs a) {
         if (f + x < Lk) set_bit(sl * L + layer_of(f + x), e[x]);
     }
   }
-  // Every wave keeps its own copy of U and of the candidate flags.
-  if (wave > 0)
-    for (int w = lane; w < W; w += kWave) uni[w] = uni0[w];
-  const int nq = (nv + kWave - 1) / kWave;
-  int par_s[Q];
-  uint32_t avail = 0, done = 0;  // bit q: slot lane + 64 q
+  if (copies && wave > 0) or_words<true>(uni, uni0, W, lane, kWave);
+  __syncthreads();
+  // Each wave's own slots: bit q of a lane is slot 4 (lane + 64 q) + wave.
+  int par_s[NPT];
+  uint32_t avail = 0, done = 0;
 #pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    par_s[q] = -2;
-    const int v = lane + q * kWave;
-    if (q < nq && v < nv) {
-      const int pn = par_of[v];
-      par_s[q] = pn < 0 ? -1 : (int)slot_of[pn];
-      if (pn < 0) avail |= 1u << q;
-    }
+  for (int q = 0; q < NPT; ++q) {
+    const int v = kWaves * (lane + q * kWave) + wave;
+    par_s[q] = v < nv ? par_of[v] : -2;
+    if (par_s[q] == -1) avail |= 1u << q;
   }
+#pragma unroll
+  for (int m = 0; m < NPT; ++m)
+    if ((viable >> m) & 1u) {
+      pv[slot[m]] = ben[m];
+      cdr[slot[m]] = cd[m];
+    }
   __syncthreads();
 
-  // (5) greedy selection, one workgroup barrier per step.
+  // (5) greedy selection.
   const int sub = lane & 15;
+  const int nq = (nv + kThreads - 1) / kThreads;
   int s = 0;
   for (; s < nv; ++s) {
     if (a.max_admit > 0 && s >= a.max_admit) break;
     // Candidates: unselected, parent selected or the root.
     int nf = 0;
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
+    for (int q = 0; q < NPT; ++q) {
       if (q < nq) {
         const bool cand = ((avail & ~done) >> q) & 1u;
         const uint64_t mask = __ballot(cand);
         if (cand)
-          list[nf + __popcll(mask & (lane == 0 ? 0ull : (~0ull >> (64 - lane))))] =
-              (uint16_t)(lane + q * kWave);
+          list[nf + __popcll(mask & below)] = (uint16_t)(kWaves * (lane + q * kWave) + wave);
         nf += __popcll(mask);
       }
     }
-    wave_sync();
-    if (nf == 0) break;  // the same in every wave
-    // Each 16-lane row of each wave scores one candidate at a time, a lane
-    // per layer; the row's last lane keeps the row's best.
+    if (copies) wave_sync();
+    else __syncthreads();  // U is everybody's
+    // Each 16-lane row scores one candidate at a time, a lane per layer; the
+    // row's last lane keeps the row's best.
     double bu = -1.0;
-    int bi = INT32_MAX, bn = 0;
-    for (int x0 = wave * 4; x0 < nf; x0 += kWaves * 4) {
+    uint32_t bsn = kNone;
+    for (int x0 = 0; x0 < nf; x0 += 4) {
       const int x = x0 + (lane >> 4);
-      int c = 0, v = 0, node = 0;
+      int c = 0, v = 0;
       if (x < nf) {
         v = list[x];
-        node = node_of[v];
-        if (v < nr) {
-          const uint32_t* rv_ = rows + (size_t)v * W;
-          for (int l = sub; l < L; l += 16) c += count_new<EW>(rv_ + l * EW, uni + l * EW);
-        } else {
-          for (int l = sub; l < L; l += 16)
-            c += count_new_ids(ids + (size_t)node * Lk + l * k, k, E, uni + l * EW);
-        }
+        const uint32_t* rv_ = rows + (size_t)v * W;
+        for (int l = sub; l < L; l += 16) c += count_new<EW>(rv_ + l * EW, uni + l * EW);
       }
       c = row16_sum(c);
       if (x < nf && sub == 15) {
-        const double u = utility(pv[node] * a.t_ar, c, a.t_exp, (double)cdr[node]);
-        if (better(u, v, bu, bi)) {
+        const double u = utility(pv[v], c, a.t_exp, (double)cdr[v]);
+        const uint32_t sn = ((uint32_t)v << kNewBits) | (uint32_t)c;
+        if (better(u, sn, bu, bsn)) {
           bu = u;
-          bi = v;
-          bn = c;
+          bsn = sn;
         }
       }
     }
     // The wave's best of its four row leaders.
     {
       double wu = readlane_f64(bu, 15);
-      int wi = __builtin_amdgcn_readlane(bi, 15), wn = __builtin_amdgcn_readlane(bn, 15);
+      uint32_t wsn = __builtin_amdgcn_readlane(bsn, 15);
 #pragma unroll
       for (int g = 1; g < 4; ++g) {
         const double gu = readlane_f64(bu, 16 * g + 15);
-        const int gi = __builtin_amdgcn_readlane(bi, 16 * g + 15);
-        if (better(gu, gi, wu, wi)) {
+        const uint32_t gsn = __builtin_amdgcn_readlane(bsn, 16 * g + 15);
+        if (better(gu, gsn, wu, wsn)) {
           wu = gu;
-          wi = gi;
-          wn = __builtin_amdgcn_readlane(bn, 16 * g + 15);
+          wsn = gsn;
         }
       }
       bu = wu;
-      bi = wi;
-      bn = wn;
+      bsn = wsn;
     }
     // Two buffers by step parity: a wave that is a step ahead writes the
     // other one, and none can be two steps ahead of the barrier.
     const int z = s & 1;
     if (lane == 0) {
-      misc->red_u[z][wave] = bu;
-      misc->red_i[z][wave] = bi;
-      misc->red_n[z][wave] = bn;
+      misc->best.u[z][wave] = bu;
+      misc->best.sn[z][wave] = bsn;
     }
     __syncthreads();
-    bu = misc->red_u[z][0];
-    bi = misc->red_i[z][0];
-    bn = misc->red_n[z][0];
+    bu = misc->best.u[z][0];
+    bsn = misc->best.sn[z][0];
 #pragma unroll
     for (int w = 1; w < kWaves; ++w)
-      if (better(misc->red_u[z][w], misc->red_i[z][w], bu, bi)) {
-        bu = misc->red_u[z][w];
-        bi = misc->red_i[z][w];
-        bn = misc->red_n[z][w];
+      if (better(misc->best.u[z][w], misc->best.sn[z][w], bu, bsn)) {
+        bu = misc->best.u[z][w];
+        bsn = misc->best.sn[z][w];
       }
-    if (bi == INT32_MAX || !(bu >= 1.0)) break;  // same decision in every thread
-    const int j = bi, node = node_of[j];
+    if (bsn == kNone || !(bu >= 1.0)) break;  // same decision in every thread
+    const int j = (int)(bsn >> kNewBits);
     if (tid == 0) {
-      a.order[node0 + s] = node;
+      a.order[node0 + s] = node_of[j];
       a.util[node0 + s] = bu;
-      a.n_new[node0 + s] = bn;
+      a.n_new[node0 + s] = (int)(bsn & ((1u << kNewBits) - 1));
     }
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
+    for (int q = 0; q < NPT; ++q) {
       if (par_s[q] == j) avail |= 1u << q;
-      if (lane + q * kWave == j) done |= 1u << q;
+      if (kWaves * (lane + q * kWave) + wave == j) done |= 1u << q;
     }
-    // U gains the selected node's experts.
-    if (j < nr) {
-      const uint32_t* rj = rows + (size_t)j * W;
-      for (int w = lane; w < W; w += kWave) uni[w] |= rj[w];
-    } else {
-      for (int f = lane; f < Lk; f += kWave) {
-        const int e = ids[(size_t)node * Lk + f];
-        if ((uint32_t)e < (uint32_t)E)
-          atomicOr(&uni[layer_of(f) * EW + (e >> 5)], 1u << (e & 31));
-      }
-    }
-    // The next step's wave_sync orders U before its scoring.
+    // U gains the selected node's experts; the next step's wave_sync or
+    // barrier orders this before its scoring.
+    const uint32_t* rj = rows + (size_t)j * W;
+    if (copies) or_words<false>(uni, rj, W, lane, kWave);
+    else or_words<false>(uni, rj, W, tid, kThreads);
   }
-  wave_sync();
+  if (copies) wave_sync();
+  else __syncthreads();
 
   // Epilogue: padding of the per-selection outputs, union size, status.
   for (int x = s + tid; x < N; x += kThreads) {
@@ -482,22 +480,36 @@ __global__ __launch_bounds__(kThreads) void expand_kernel(ExpandArgs a) {
   }
 }
 
+// A workgroup per tree, dealt to whichever unit is free.  kLeftOnly: a later
+// launch, where only those whose tree was left do anything.
+template <int NPT, int EW, bool kLeftOnly>
+__global__ __launch_bounds__(kThreads, 4) void expand_kernel(ExpandArgs a) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  if (kLeftOnly && a.n_admit[blockIdx.x] != kLeft) return;
+  expand_tree<NPT, EW>(a, lds, blockIdx.x);
+}
+
 // Bitsets that a workgroup of at most `budget` bytes of LDS holds.
-int slots_in(const ExpandArgs& a, size_t budget) {
+int slots_in(const ExpandArgs& a, size_t budget, int copies) {
+  int c = a.N;
+  const size_t all = expand_lds(a.N, a.L, a.E, c, copies).total;
   const size_t row = (size_t)a.L * expand_words(a.E) * 4;
-  const size_t fixed = expand_lds(a.N, a.L, a.E, 0).total;
-  return (int)min((size_t)a.N, budget > fixed ? (budget - fixed) / row : (size_t)0);
+  if (all > budget) c = (int)max((long)0, (long)c - (long)((all - budget + row - 1) / row));
+  while (c > 0 && expand_lds(a.N, a.L, a.E, c, copies).total > budget) --c;
+  return c;
 }
 
 template <int NPT, int EW>
 hipError_t launch_ew(const ExpandArgs& a, size_t lds_bytes, hipStream_t s) {
-  const void* fn = reinterpret_cast<const void*>(&expand_kernel<NPT, EW>);
+  const auto kernel =
+      a.left_only ? expand_kernel<NPT, EW, true> : expand_kernel<NPT, EW, false>;
   if (lds_bytes > 65536) {
-    const hipError_t e =
-        hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             (int)lds_bytes);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((expand_kernel<NPT, EW>), dim3(a.T), dim3(kThreads), lds_bytes, s, a);
+  hipLaunchKernelGGL(kernel, dim3(a.T), dim3(kThreads), lds_bytes, s, a);
   return hipGetLastError();
 }
 
@@ -515,7 +527,7 @@ hipError_t launch_npt(const ExpandArgs& a, size_t lds_bytes, hipStream_t s) {
 }
 
 hipError_t launch_one(const ExpandArgs& a, hipStream_t s) {
-  const size_t lds_bytes = expand_lds(a.N, a.L, a.E, a.cap).total;
+  const size_t lds_bytes = expand_lds(a.N, a.L, a.E, a.cap, a.copies).total;
   if (a.N <= kThreads) return launch_npt<1>(a, lds_bytes, s);
   if (a.N <= 2 * kThreads) return launch_npt<2>(a, lds_bytes, s);
   return launch_npt<4>(a, lds_bytes, s);
@@ -523,17 +535,24 @@ hipError_t launch_one(const ExpandArgs& a, hipStream_t s) {
 
 }  // namespace
 
-// Trees that do not fill the compute units, and trees whose bitsets all fit a
-// quarter of a unit's LDS, take one launch.  Otherwise one launch with a
-// quarter (four workgroups a unit) takes the trees whose viable nodes fit,
-// and a second one with half takes the rest.  Measured on MI355X, 1024
-// Qwen3-shaped trees (768 bytes a node, 44 slots in 40 KB) by T_AR: 512 26
-// us with the two launches (41 with one at half), 8192, where most trees are
-// left, 256 (188); one launch at a quarter with the nodes beyond it counted
-// from their ids 25 and 672, the bitsets of all nodes in one workgroup a unit
-// with the next tree's ids prefetched 121 and 432.
+// The launches of a call: one that keeps the bitsets of every node, unless
+// the trees outnumber the compute units.  Then first one whose workgroups take
+// half of a unit's LDS each (a quarter from two trees a unit on), which leaves
+// the trees with more viable nodes than its bitsets to the next.
+// Measured on MI355X, 1024 Qwen3-shaped trees (116 nodes of 768 bytes; 46
+// bitsets in a quarter, 100 in a half) by T_AR, against one launch of one
+// workgroup a unit: 512 27 us (118), 8192, where most trees pass the quarter,
+// 234 (440; 299 without the half), 100000 712 (820).  Empty later launches cost
+// about 1 us each.  Where each launch leaves every tree and the last one selects
+// nothing, the others are lost: 300 trees of 28 nodes of 4 KB 35 us (26).
+//
+// The copies of U: one per wave up to kCopyWords words, where it does not
+// cost the last bitset.  One Qwen3-shaped tree of 57 selections (192 words)
+// 102 us against 104 with a single U; L = 48, E = 256, 52 selections (384 words)
+// 91.4 against 89.9, L = 64, E = 512, 28 selections (1024 words) 64 against 60.
 constexpr size_t kQuarterLds = 40 * 1024, kHalfLds = 80 * 1024;
-constexpr int kMinSlots = 16;
+constexpr int kMinSlots = 16;     // a launch with fewer bitsets would leave nearly every tree
+constexpr int kCopyWords = 256;
 
 hipError_t launch_expand(const ExpandArgs& a_in, size_t lds_limit, hipStream_t s) {
   if (a_in.T == 0) return hipSuccess;
@@ -542,22 +561,28 @@ hipError_t launch_expand(const ExpandArgs& a_in, size_t lds_limit, hipStream_t s
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
   ExpandArgs a = a_in;
-  const int most = slots_in(a, lds_limit);  // the fixed part alone is at most 66000 bytes
-  const int quarter = slots_in(a, kQuarterLds);
-  a.pass = kAllTrees;
-  a.cap = most;
-  if (a.T <= cus || quarter >= a.N) {
-    if (a.T > cus) a.cap = a.N;
-    return launch_one(a, s);
+  a.left_only = false;
+  const int words = a.L * expand_words(a.E);
+  const struct {
+    size_t lds;
+    int min_slots;  // fewer bitsets than this: not this launch
+    int trees;      // nor for this many trees or fewer
+  } launches[] = {{kQuarterLds, min(kMinSlots, a.N), 2 * cus},
+                  {kHalfLds, min(kMinSlots, a.N), cus},
+                  {lds_limit, a.N, 0}};
+  for (const auto& l : launches) {
+    if (a.T <= l.trees) continue;
+    const int single = slots_in(a, l.lds, 1), copied = slots_in(a, l.lds, kExpandWaves);
+    const bool all = single == a.N && copied < a.N;  // the copies would cost the last bitset
+    a.copies = words <= kCopyWords && !all && copied >= l.min_slots ? kExpandWaves : 1;
+    a.cap = a.copies == 1 ? single : copied;
+    if (a.cap < l.min_slots) continue;
+    a.leave = a.cap < a.N;
+    if ((e = launch_one(a, s)) != hipSuccess || !a.leave) return e;
+    a.left_only = true;
   }
-  if (quarter >= kMinSlots) {
-    a.pass = kFitting;
-    a.cap = quarter;
-    if ((e = launch_one(a, s)) != hipSuccess) return e;
-    a.pass = kRest;
-  }
-  a.cap = min(most, max(slots_in(a, kHalfLds), kMinSlots));
-  return launch_one(a, s);
+  // An accepted shape's N bitsets and one union fit the last launch.
+  return hipErrorInvalidValue;
 }
 
 }  // namespace s2moe

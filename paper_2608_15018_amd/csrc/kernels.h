@@ -157,15 +157,18 @@ struct ExpandArgs {
   int T, N, L, E, k, max_admit;
   uint64_t k_div;    // ceil(2^42 / k): f / k == (f * k_div) >> 42 for f < 2^22, k <= 32
   uint64_t cpn_div;  // the same for ceil(L k / 4), the 4-id chunks of a node (<= 1024)
-  int cap;           // nodes of a tree whose bitsets are kept in LDS (set by launch_expand)
-  int pass;          // which trees the launch takes (set by launch_expand)
+  // Set by launch_expand:
+  int cap;         // nodes of a tree whose bitsets are kept in LDS
+  int copies;      // copies of the union in LDS: one per wave, or 1
+  bool left_only;  // take only the trees that an earlier launch left
+  bool leave;      // leave the trees of more than cap viable nodes
   double t_ar, t_exp;
 };
 
 // Byte offsets of the expansion kernel's LDS regions; host and device use
 // the same function so the launch size and the carve-up agree.
 struct ExpandLds {
-  size_t pv, rows, uni, cdr, node, slot, par, list, misc, total;
+  size_t misc, rows, uni, pv, cdr, node, list, total;
 };
 
 constexpr int kExpandWaves = 4;  // waves of a workgroup
@@ -176,23 +179,23 @@ __host__ __device__ inline int expand_words(int E) {
   return w;
 }
 
-// Layout for N nodes with the expert bitsets of `cap` of them.
-__host__ __device__ inline ExpandLds expand_lds(int N, int L, int E, int cap) {
+// Layout for N nodes with the expert bitsets of `cap` of them and `copies`
+// unions.  With all N bitsets and one union it never needs more than
+// expand_accept_bytes, whatever the shape: every accepted tree can keep its
+// bitsets in LDS.
+__host__ __device__ inline ExpandLds expand_lds(int N, int L, int E, int cap, int copies) {
   const size_t row = (size_t)L * expand_words(E) * 4;
   ExpandLds o;
   size_t off = 0;
-  o.misc = off;   off += 256;                        // reductions and counters
-  o.pv = off;     off += (size_t)N * 8;              // p_i (double)
-  off = (off + 15) & ~(size_t)15;
+  o.misc = off;   off += 112;                        // reductions and counters
   o.rows = off;   off += (size_t)cap * row;          // expert bitset per (slot, layer)
-  off = (off + 15) & ~(size_t)15;
-  o.uni = off;    off += kExpandWaves * row;         // union bitset per layer, per wave
-  o.cdr = off;    off += (size_t)N * 4;              // C^draft
+  o.uni = off;    off += (size_t)copies * row;       // union bitset per layer
+  off = (off + 7) & ~(size_t)7;
+  o.pv = off;     off += (size_t)N * 8;              // p per node, then benefit per slot (double)
+  o.cdr = off;    off += (size_t)N * 4;              // C^draft per slot
   o.node = off;   off += (size_t)N * 2;              // node of a slot
-  o.slot = off;   off += (size_t)N * 2;              // slot of a node
-  o.par = off;    off += (size_t)N * 2;              // parent node of a slot
-  o.list = off;   off += kExpandWaves * (size_t)N * 2;  // candidate list, per wave
-  o.total = (off + 15) & ~(size_t)15;
+  o.list = off;   off += (size_t)((N + kExpandWaves - 1) / kExpandWaves) * kExpandWaves * 2;
+  o.total = (off + 15) & ~(size_t)15;                // list: parents' slots, then candidates
   return o;
 }
 
