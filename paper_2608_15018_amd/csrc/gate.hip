@@ -11,7 +11,8 @@
 //   * per token (a team of lanes: a wave, or a 16-lane row of one so that the
 //     workgroup takes 64 tokens at a time): biased order keys, the exact top-k
 //     by taking the team's largest key k times (ties to the lower expert id),
-//     a scan for ascending-id order, a softmax over the team;
+//     or by the threshold search where k is large (team_max_k), ascending-id
+//     order, a softmax over the team;
 //   * buckets: a B-bit token mask per expert (LDS 64-bit ORs), so an
 //     assignment's position in its expert's list is the popcount of the mask
 //     below its token.
@@ -47,13 +48,15 @@ __device__ __forceinline__ void load_row(const float* ell, int e0, int E, bool r
 }
 
 // kG = lanes of a token's team, kS = expert slots per lane (E <= kG kS).
-// kSelect (with
-// kStaged): the kernel first ranks every token's staged logits itself and
-// writes plain_idx and gap, instead of reading them from a routing launch
-// (ra: the routing step's arguments).
-template <bool kStaged, int kG, int kS, bool kSelect>
+// kNT = 0: teams rank by taking maxima; else whole waves (kG = 64), kNT tokens
+// at a time, by the threshold search.  kSelect (with kStaged): the kernel first
+// ranks every token's staged logits itself and writes plain_idx and gap,
+// instead of reading them from a routing launch (ra: the routing step's
+// arguments).
+template <bool kStaged, int kG, int kS, int kNT, bool kSelect>
 __global__ __launch_bounds__(1024) void reuse_gate_kernel(GateArgs a, RouteArgs ra) {
   static_assert(kStaged || !kSelect, "ranking reads the staged logits");
+  static_assert(kNT == 0 || kG == kWave, "the search ranks by wave");
   constexpr int kMaskWords = kMaxTokens / 64;
   constexpr int kNJ = (kG * kS + 63) / 64;  // expert slots per lane of TopCap's wave
   __shared__ __align__(16) float ell_s[kStaged ? kStage : 1];
@@ -111,7 +114,12 @@ __global__ __launch_bounds__(1024) void reuse_gate_kernel(GateArgs a, RouteArgs 
   // Team t of wave w takes tokens kTeams w + t, + kTeams n_waves, ...
   constexpr int kTeams = kWave / kG;
   const int team = lane / kG, e0 = (lane % kG) * kS;
-  if (kSelect) {
+  if (kSelect && kNT > 0) {
+    for (int b = wave; b < B; b += n_waves)
+      wave_select_plain<kNJ>(E, k, ell + (size_t)b * E, plain_s + b * k, gap_s + b,
+                             ra.plain_idx + (size_t)b * k, ra.gap + b);
+    __syncthreads();
+  } else if (kSelect) {
     // Exact top-(k+1) by (value desc, id asc): the last one taken is the
     // (k+1)-th, the others are the plain top-k.
     for (int b0 = wave * kTeams; b0 < B; b0 += n_waves * kTeams) {
@@ -207,7 +215,71 @@ __global__ __launch_bounds__(1024) void reuse_gate_kernel(GateArgs a, RouteArgs 
 
   // Per token: lambda_b, biased keys, biased top-k, gate weights, masks.
   const bool from_biased = (a.flags & kGateFromBiased) != 0;
-  for (int b0 = wave * kTeams; b0 < B; b0 += n_waves * kTeams) {
+  if constexpr (kNT > 0) {
+    // Wave w takes tokens w, w + 16, ...; kNT of them at a time.
+    for (int b0 = wave; b0 < B; b0 += n_waves * kNT) {
+      float l[kNT][kNJ], lb[kNT][kNJ];
+      uint32_t key[kNT][kNJ];
+#pragma unroll
+      for (int t = 0; t < kNT; ++t) {
+        const int b = b0 + t * n_waves;
+        float lam = 0.f;
+        if (active && b < B) lam = (a.flags & kBiasAbsolute) ? a.alpha : a.alpha * gap_s[b];
+#pragma unroll
+        for (int j = 0; j < kNJ; ++j) {
+          const int e = lane + kWave * j;
+          l[t][j] = 0.f;
+          lb[t][j] = 0.f;
+          key[t][j] = 0;
+          if (b < B && e < E) {
+            l[t][j] = ell[(size_t)b * E + e];
+            lb[t][j] = pref_s[e] ? l[t][j] + lam : l[t][j];
+            key[t][j] = order_key(lb[t][j]);
+          }
+        }
+      }
+      uint32_t bits[kNT];
+      wave_top_k<kNT, kNJ>(key, k, bits);
+      float ez[kNT][kNJ], sum[kNT], inv_s[kNT];
+#pragma unroll
+      for (int t = 0; t < kNT; ++t) {
+        uint32_t mk = 0;
+#pragma unroll
+        for (int j = 0; j < kNJ; ++j)
+          if ((bits[t] >> j) & 1u) mk = max(mk, from_biased ? key[t][j] : order_key(l[t][j]));
+        const float m = key_value(wave_max_key_dpp(mk));
+        sum[t] = 0.f;
+#pragma unroll
+        for (int j = 0; j < kNJ; ++j) {
+          const float x = from_biased ? lb[t][j] : l[t][j];
+          ez[t][j] = ((bits[t] >> j) & 1u) ? __builtin_amdgcn_exp2f((x - m) * kLog2e) : 0.f;
+          sum[t] += ez[t][j];
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < kNT; ++t) inv_s[t] = __builtin_amdgcn_rcpf(wave_sum_dpp(sum[t]));
+#pragma unroll
+      for (int t = 0; t < kNT; ++t) {
+        const int b = b0 + t * n_waves;
+        if (b >= B) break;
+        int rank[kNJ];
+        wave_rank_flagged<kNJ>(bits[t], rank);
+#pragma unroll
+        for (int j = 0; j < kNJ; ++j) {
+          if ((bits[t] >> j) & 1u) {
+            const int pos = b * k + rank[j];
+            const int e = lane + kWave * j;
+            a.idx[pos] = e;
+            a.gate_w[pos] = ez[t][j] * inv_s[t];
+            idx_s[pos] = (uint8_t)e;
+            atomicOr(reinterpret_cast<unsigned long long*>(&mask_s[e][b >> 6]),
+                     1ull << (b & 63));
+          }
+        }
+      }
+    }
+  }
+  for (int b0 = kNT > 0 ? B : wave * kTeams; b0 < B; b0 += n_waves * kTeams) {
     const int b = b0 + team;
     const bool real = b < B;
     float lam = 0.f;
@@ -339,9 +411,44 @@ __global__ __launch_bounds__(kWave) void route_gate_small_kernel(RouteArgs ra, G
   small_route_gate<kNJ>(ra, a, s, true);
 }
 
-template <bool kStaged, bool kSelect, int kG, int kS>
+template <bool kStaged, bool kSelect, int kG, int kS, int kNT = 0>
 void launch_gate_team(const GateArgs& a, const RouteArgs& ra, hipStream_t s) {
-  hipLaunchKernelGGL((reuse_gate_kernel<kStaged, kG, kS, kSelect>), dim3(1), dim3(1024), 0, s, a, ra);
+  hipLaunchKernelGGL((reuse_gate_kernel<kStaged, kG, kS, kNT, kSelect>), dim3(1), dim3(1024), 0, s,
+                     a, ra);
+}
+
+// Largest k that the teams rank by taking maxima; more go to the threshold
+// search, whose length does not depend on k.  A line lies where the gating
+// launches cross; MI355X, us by the search and by taking maxima: 8 tokens, 64
+// experts, k = 3 / 4 / 8 / 16 5.8 / 5.8 / 6.0 / 6.0 and 5.6 / 5.9 / 6.3 / 7.0;
+// 16 tokens, 128 experts, k = 7 / 8 / 16 7.5 / 7.4 / 7.6 and 7.5 / 7.5 / 8.8;
+// 32 tokens, 256 experts, k = 6 / 8 / 16 12.1 / 12.2 / 12.7 and 11.9 / 12.6 /
+// 15.3; 64 tokens, 128 experts, k = 8 / 13 / 16 12.6 / 12.8 / 12.8 and 10.8 /
+// 12.6 / 13.5; 256 tokens, 64 experts, k = 8 / 16 24.3 / 25.5 and 17.5 / 24.8.
+int team_max_k(int B, int E) {
+  if (E <= 16) return B <= 8 ? 8 : kMaxTopK;
+  if (B <= 8) return E <= 64 ? 3 : E <= 128 ? 6 : 7;
+  if (B <= 16) return E <= 64 ? 5 : E <= 128 ? 7 : 8;
+  if (B <= 32) return E <= 64 ? 12 : E <= 128 ? 8 : 6;
+  return E <= 64 ? kMaxTopK : 13;
+}
+
+bool gate_by_search(const GateArgs& a) { return a.k > team_max_k(a.B, a.E); }
+
+// Waves take 1, 2 or 4 tokens at a time, so that their searches' chains
+// overlap.  Logits that are not staged are those of 41 tokens and more.
+template <bool kStaged, bool kSelect, int kNJ>
+void launch_gate_search(const GateArgs& a, const RouteArgs& ra, hipStream_t s) {
+  if constexpr (kSelect)
+    launch_gate_team<kStaged, true, 64, kNJ, 1>(a, ra, s);  // at most 16 tokens
+  else if constexpr (!kStaged)
+    launch_gate_team<false, false, 64, kNJ, 4>(a, ra, s);
+  else if (a.B <= 16)
+    launch_gate_team<true, false, 64, kNJ, 1>(a, ra, s);
+  else if (a.B <= 32)
+    launch_gate_team<true, false, 64, kNJ, 2>(a, ra, s);
+  else
+    launch_gate_team<true, false, 64, kNJ, 4>(a, ra, s);
 }
 
 // Up to 16 tokens each of the 16 waves has at most one, and a whole wave per
@@ -353,13 +460,23 @@ constexpr int kWaveTeamMaxTokens = 16;
 
 template <bool kStaged, bool kSelect>
 void launch_gate_staged(const GateArgs& a, const RouteArgs& ra, hipStream_t s) {
-  const bool wide = a.B <= kWaveTeamMaxTokens;
-  if (a.E <= 16) launch_gate_team<kStaged, kSelect, 16, 1>(a, ra, s);
-  else if (a.E <= 64 && wide) launch_gate_team<kStaged, kSelect, 64, 1>(a, ra, s);
-  else if (a.E <= 64) launch_gate_team<kStaged, kSelect, 16, 4>(a, ra, s);
-  else if (a.E <= 128 && wide) launch_gate_team<kStaged, kSelect, 64, 2>(a, ra, s);
+  if (gate_by_search(a)) {
+    if (a.E <= 64) launch_gate_search<kStaged, kSelect, 1>(a, ra, s);
+    else if (a.E <= 128) launch_gate_search<kStaged, kSelect, 2>(a, ra, s);
+    else launch_gate_search<kStaged, kSelect, 4>(a, ra, s);
+    return;
+  }
+  if constexpr (kStaged) {
+    if (a.E <= 16) return launch_gate_team<true, kSelect, 16, 1>(a, ra, s);
+    if (a.B <= kWaveTeamMaxTokens) {
+      if (a.E <= 64) launch_gate_team<true, kSelect, 64, 1>(a, ra, s);
+      else if (a.E <= 128) launch_gate_team<true, kSelect, 64, 2>(a, ra, s);
+      else launch_gate_team<true, kSelect, 64, 4>(a, ra, s);
+      return;
+    }
+  }
+  if (a.E <= 64) launch_gate_team<kStaged, kSelect, 16, 4>(a, ra, s);
   else if (a.E <= 128) launch_gate_team<kStaged, kSelect, 16, 8>(a, ra, s);
-  else if (wide) launch_gate_team<kStaged, kSelect, 64, 4>(a, ra, s);
   else launch_gate_team<kStaged, kSelect, 16, 16>(a, ra, s);
 }
 
@@ -392,15 +509,19 @@ hipError_t launch_reuse_gate(const GateArgs& a, hipStream_t s) {
 // 94.6 against 92.6 us, but at 64 tokens 65.7 against 66.6; 64 experts, where
 // one workgroup per token also computes the logits, at 12 / 24 / 64 tokens
 // 39.5 / 56.6 / 142 against 37.5 / 54.4 / 140 us, at 100 tokens 81.2 against
-// 82.6.
-constexpr int kGateSelectMaxTokens = 32;
-constexpr int kGateSelectMaxTokens64 = 64;  // up to 64 experts
+// 82.6, and at 64 tokens of a small layer by k = 6 / 8 / 9 / 12 / 16 30.0 /
+// 30.7 / 31.7 / 33.2 / 34.0 against 29.3 / 30.5 / 31.7 / 33.8 / 35.5.
+int gate_select_max_tokens(const GateArgs& a) {
+  if (gate_by_search(a)) return 16;  // a token a wave
+  if (a.E > 64) return 32;
+  return a.E <= 16 || a.k <= 8 ? 64 : 32;
+}
 
 hipError_t launch_route_and_gate(const RouteArgs& ra, const GateArgs& a, hipStream_t s) {
   const bool small = small_gate_applies(a) && route_ranks_separately(ra);
   const bool select = (route_ranks_separately(ra) || route_rows_same_bits(ra)) &&
                       a.B * a.E <= kStage &&
-                      a.B <= (a.E <= 64 ? kGateSelectMaxTokens64 : kGateSelectMaxTokens);
+                      a.B <= gate_select_max_tokens(a);
   if (!small && !select) {
     const hipError_t err = launch_route(ra, s);
     return err != hipSuccess ? err : launch_reuse_gate(a, s);

@@ -1,6 +1,7 @@
 """The gating kernel's per-token ranking by teams of lanes (a wave, or a row of
-16 lanes) against the fp64 oracle on dyadic logits with many exact ties, and
-the one-call layer's ranking inside the gating launch against the four calls."""
+16 lanes) and by the threshold search, against the fp64 oracle on dyadic
+logits with many exact ties, and the one-call layer's ranking inside the gating
+launch against the four calls."""
 
 import numpy as np
 import pytest
@@ -16,17 +17,23 @@ torch = pytest.importorskip("torch")
 
 # Expert counts at the edges of a team's slots (1, 4, 8, 16 a row lane; 1, 2, 4
 # a wave lane) and not multiples of 4; token counts at the edges of a wave per
-# token (16), of a row group (4) and of a workgroup pass (64).
-@pytest.mark.parametrize("E,k,cap", [(2, 1, 1), (3, 2, 2), (16, 15, 16), (17, 16, 17), (63, 6, 9),
-                                     (64, 8, 16), (66, 3, 40), (127, 16, 20), (128, 8, 14),
-                                     (129, 5, 7), (255, 16, 30), (256, 12, 100)])
+# token (16), of a row group (4) and of a workgroup pass (64).  k at the edges
+# of taking maxima: by 8, 16, 32 and more tokens up to 3 / 5 / 12 / 16 of 17 to
+# 64 experts, 6 / 7 / 8 / 13 of 65 to 128, 7 / 8 / 6 / 13 of more, 8 / 16 / 16 /
+# 16 of at most 16.
+@pytest.mark.parametrize("E,k,cap", [(2, 1, 1), (3, 2, 2), (16, 8, 12), (16, 9, 12), (16, 15, 16),
+                                     (17, 16, 17), (63, 5, 9), (63, 6, 9), (64, 3, 12),
+                                     (64, 4, 12), (64, 12, 16), (64, 13, 16), (66, 3, 40),
+                                     (127, 16, 20), (128, 7, 14), (128, 8, 14), (128, 9, 14),
+                                     (129, 5, 7), (200, 6, 9), (200, 7, 9), (255, 16, 30),
+                                     (256, 11, 100), (256, 13, 100), (256, 14, 100)])
 def test_ties_over_team_edges(E, k, cap):
     import paper_2608_15018_amd as s2
     rng = np.random.default_rng(E * 31 + k)
     H = -(-E // 64) * 64
     router = np.zeros((E, H), np.float32)
     router[np.arange(E), np.arange(E)] = 1.0
-    for B in (1, 3, 5, 16, 17, 63, 65, 256):
+    for B in (1, 3, 5, 8, 9, 16, 17, 32, 33, 63, 65, 256):
         # eighths in [-2, 2]: with alpha 0.5 every g, bias and biased logit is exact
         x = np.zeros((B, H), np.float32)
         x[:, :E] = rng.integers(-16, 17, size=(B, E)) / 8.0
@@ -49,12 +56,23 @@ def test_ties_over_team_edges(E, k, cap):
             assert np.abs(got["gate_w"] - ref["gate_w"]).max() <= 5e-6, label
 
 
-@pytest.mark.parametrize("E,k,B", [(40, 4, 9), (64, 6, 33), (64, 6, 64), (64, 6, 65), (36, 3, 24),
-                                   (100, 8, 17), (128, 8, 32), (128, 8, 33), (32, 4, 24)])
-def test_ranking_inside_the_gating_launch(E, k, B):
-    shape = LayerShape(hidden=256, ffn=64, n_experts=E, top_k=k, cap=2 * k, alpha=0.5)
+# hidden 256: logits in one slice of H, as the rows launch adds them.  1024
+# (512 in fp32): the routing slices H for 32 experts and fewer, where the gate
+# must not rank what the rows launch would compute, but not for 36.  k beyond
+# taking maxima: ranked by the search, up to 16 tokens inside the launch.
+@pytest.mark.parametrize("E,k,B,hidden,act", [
+    (40, 4, 9, 256, "bf16"), (64, 6, 33, 256, "bf16"), (64, 6, 64, 256, "bf16"),
+    (64, 6, 65, 256, "bf16"), (36, 3, 24, 256, "bf16"), (100, 8, 17, 256, "bf16"),
+    (128, 8, 32, 256, "bf16"), (128, 8, 33, 256, "bf16"), (32, 4, 24, 256, "bf16"),
+    (32, 4, 24, 1024, "bf16"), (8, 2, 40, 1024, "bf16"), (36, 4, 24, 1024, "bf16"),
+    (32, 4, 24, 512, "f32"), (32, 4, 24, 256, "f32"), (36, 4, 40, 512, "f32"),
+    (64, 10, 12, 256, "bf16"), (64, 10, 40, 256, "bf16"), (16, 9, 40, 256, "bf16"),
+    (200, 12, 16, 256, "bf16"), (200, 12, 17, 256, "bf16"), (64, 13, 32, 256, "bf16")])
+def test_ranking_inside_the_gating_launch(E, k, B, hidden, act):
+    shape = LayerShape(hidden=hidden, ffn=64, n_experts=E, top_k=k, cap=min(E, 2 * k), alpha=0.5,
+                       act=act, wdt=act)
     d = make_inputs(shape, B, seed=E + B, rho=0.5)
-    label = f"E={E} k={k} B={B}"
+    label = f"E={E} k={k} B={B} H={hidden} {act}"
     log(f"[gate] one call {label}")
     four, dw = run_gpu(shape, d)
     one, _ = run_gpu(shape, d, dw, fused=True)
