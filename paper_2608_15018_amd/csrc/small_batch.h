@@ -58,12 +58,15 @@ __device__ __forceinline__ void wave_sync() {
 // member (smallest value, then largest id) is the (k+1)-th, the other k are
 // the plain top-k, written in id order to idx[0..k); gap = ell_(1) -
 // ell_(k+1) to *gap.  idx2 / gap2, when not null, get the same values.
-// Below kTakeMaxK experts the largest key is taken k + 1 times (a DPP chain
-// each); more of them cost more than the threshold search's 16 ballot steps.
-// Draft steps on MI355X, by the search and by taking maxima: Qwen3-shaped, 3
-// experts, 1 / 4 tokens 857 / 1627 -> 832 / 1522 us; GPT-OSS-shaped, 2 tokens
-// 1079 -> 1026; OLMoE-shaped int4, 3 tokens 335 -> 321 us.
-constexpr int kTakeMaxK = 12;
+// Up to take_max_k(NJ) experts the largest key is taken k + 1 times (a DPP
+// chain each); more of them cost more than the threshold search's 16 ballot
+// steps, which are longer the more slots a lane has.  One-call layers on
+// MI355X, by the search and by taking maxima: 64 experts, 4 tokens, k = 4 / 6 /
+// 8 18.2 / 22.9 / 22.6 against 17.8 / 23.1 / 23.6 us; 128 experts, k = 4 / 7 /
+// 9 22.2 / 26.2 / 28.0 against 20.1 / 25.5 / 27.9; 256 experts, k = 8 / 11
+// 32.0 / 34.5 against 30.0 / 33.5.  Draft steps: Qwen3-shaped, 3 experts, 1 / 4
+// tokens 857 / 1627 -> 832 / 1522 us; OLMoE-shaped int4, 3 tokens 335 -> 321.
+__host__ __device__ constexpr int take_max_k(int NJ) { return NJ == 1 ? 5 : NJ == 2 ? 8 : 11; }
 
 template <int NJ, class I1, class I2>
 __device__ __forceinline__ void wave_select_plain(int E, int k, const float* ell, I1* idx,
@@ -71,7 +74,8 @@ __device__ __forceinline__ void wave_select_plain(int E, int k, const float* ell
   const int lane = threadIdx.x & (kWave - 1);
   uint32_t bits = 0, top, low;
   int rank[NJ];
-  if (k < kTakeMaxK) {
+  const bool take = k <= take_max_k(NJ);
+  if (take) {
     uint32_t key[NJ], rest = 0;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
@@ -115,7 +119,7 @@ __device__ __forceinline__ void wave_select_plain(int E, int k, const float* ell
       if (((sel[0] >> j) & 1u) && lane + kWave * j != last) bits |= 1u << j;
     wave_rank_flagged<NJ>(bits, rank);
   }
-  const int e0 = k < kTakeMaxK ? lane * NJ : lane, de = k < kTakeMaxK ? 1 : kWave;
+  const int e0 = take ? lane * NJ : lane, de = take ? 1 : kWave;
 #pragma unroll
   for (int j = 0; j < NJ; ++j)
     if ((bits >> j) & 1u) {

@@ -20,7 +20,7 @@ torch = pytest.importorskip("torch")
 # token (16), of a row group (4) and of a workgroup pass (64).  k at the edges
 # of taking maxima: by 8, 16, 32 and more tokens up to 3 / 5 / 12 / 16 of 17 to
 # 64 experts, 6 / 7 / 8 / 13 of 65 to 128, 7 / 8 / 6 / 13 of more, 8 / 16 / 16 /
-# 16 of at most 16.
+# 16 of at most 16; in the routing's ranking up to 5, 8 and 11.
 @pytest.mark.parametrize("E,k,cap", [(2, 1, 1), (3, 2, 2), (16, 8, 12), (16, 9, 12), (16, 15, 16),
                                      (17, 16, 17), (63, 5, 9), (63, 6, 9), (64, 3, 12),
                                      (64, 4, 12), (64, 12, 16), (64, 13, 16), (66, 3, 40),
