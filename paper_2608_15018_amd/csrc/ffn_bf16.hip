@@ -371,8 +371,8 @@ hipError_t launch_mode(const FfnArgs& a, int spw, hipStream_t s) {
 // For 17-32 tokens the down projection (a short K: 24 steps at F = 768)
 // splits K over 4 waves of 6 steps: measured on MI355X at 32 tokens over
 // 128 experts, its launch then takes 2 us less than with one wave (8 waves:
-// 15 us more).  For 33 tokens and more two waves split every K, also a short
-// one, as the wide kernel does.
+// 15 us more).  Above 32 tokens two waves split every K, as the wide kernel's
+// groups do (launch_bf16_large).
 #ifndef S2MOE_BF16_TINY
 #define S2MOE_BF16_TINY 1, 1, 2, 1, 4, 16
 #endif
@@ -383,14 +383,33 @@ hipError_t launch_mode(const FfnArgs& a, int spw, hipStream_t s) {
 #define S2MOE_BF16_MEDIUM 2, 2, 2, 2, 2, 32, 4
 #endif
 
-#ifndef S2MOE_BF16_LARGE
-#define S2MOE_BF16_LARGE 4, 2, 1, 4, 1, 1
-#endif
-
 template <int TMAX, int RG, int UG, int RD, int UD, int SPW, int SPWD = SPW>
 hipError_t launch_bf16_pair(const FfnArgs& a, hipStream_t s) {
   hipError_t err = launch_mode<0, TMAX, RG, UG>(a, SPW, s);
   return err != hipSuccess ? err : launch_mode<1, TMAX, RD, UD>(a, SPWD, s);
+}
+
+// 33 tokens and more, where the wide kernel does not apply: four token tiles
+// at once, K split over two waves, except a down projection of so short a K
+// that one wave takes it (H = 4096, F = 64, 256 experts, 64 tokens:
+// 96 us by two, 80 by one).
+constexpr int kLargeOneWaveF = 256;
+
+template <int kMode, int R, int W, int U>
+hipError_t launch_large_mode(const FfnArgs& a, hipStream_t s) {
+  const dim3 grid(n_blocks(a, kMode, 16 * R)), block(64 * W);
+  if (a.packed)
+    hipLaunchKernelGGL((ffn_bf16_kernel<kMode, 4, R, W, U, true>), grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL((ffn_bf16_kernel<kMode, 4, R, W, U, false>), grid, block, 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_bf16_large(const FfnArgs& a, hipStream_t s) {
+  const hipError_t err = launch_large_mode<0, 2, 2, 1>(a, s);
+  if (err != hipSuccess) return err;
+  return a.ldh < kLargeOneWaveF ? launch_large_mode<1, 4, 1, 1>(a, s)
+                                : launch_large_mode<1, 4, 2, 1>(a, s);
 }
 
 // The fused small-batch layer with the tiny-batch configuration above: the
@@ -464,25 +483,40 @@ hipError_t launch_moe_layer_small_bf16(const RouteArgs& ra, const GateArgs& ga,
                   : TinyLayer::layer<false>(ra, ga, a, y, s);
 }
 
-// Batches of more tokens than this run on ffn_bf16_wide.hip.  Step times on
-// MI355X, this file's kernel against it: packed weights, H = 4096,
-// F = 14336, 8 experts at 64 / 80 / 128 / 256 tokens 431 / 457 / 573 / 955
-// against 454 / 461 / 487 / 559 us; 128 experts of F = 768 at 70 / 128 tokens
-// 131 / 176 against 134 / 166 us.  Row-major weights, where 32-row units read
-// 128 bytes of a row at a time: 37 tokens at H = F = 2880, 128 experts 395
-// against 351 us, 48 tokens at F = 1024, 64 experts 142 against 137 us, but
-// 24 tokens at F = 768 105 against 107 us.  From 33 tokens to kWideMinPacked
-// both layouts add the same two K parts in the same order, so their results
-// are equal bit for bit (as up to 16; between, k_share).
-constexpr int kWideMinPacked = 96;
-constexpr int kWideMinRows = 32;
+// Which batches run on ffn_bf16_wide.hip.  Step times on MI355X, the kernel of
+// this file at 33 tokens and more against it:
+// - Packed weights, H = 4096, F = 14336, 8 experts at 64 / 80 / 128 / 256
+//   tokens 431 / 457 / 573 / 955 against 454 / 461 / 487 / 559 us; 128 experts
+//   of F = 768 at 70 / 128 tokens 131 / 176 against 134 / 166 us.
+// - Row-major weights, where 32-row units read 128 bytes of a row at a time:
+//   37 tokens at H = F = 2880, 128 experts 395 against 351 us, 48 tokens at
+//   F = 1024, 64 experts 142 against 137 us, but 24 tokens at F = 768 105
+//   against 107 us.
+// - Its units are 64 rows and cost more to start, so few or short ones are
+//   slower until buckets of more than 64 tokens would take the other kernel
+//   further passes.  Its time over the other's, geometric means over 8 to 256
+//   experts, H and F of 1024 to 4096, by gate-up units 64 / 128 / 256 / 512:
+//   row-major, 33 tokens 1.22 / 1.18 / 1.07 / 0.95, 128 tokens 0.97 / 0.96 /
+//   0.89 / 0.86; packed, 97 tokens 1.05 / 1.04 / 0.97 / 0.98.  By F from 256
+//   units on, 64 / 128 / 256 / 512: row-major, 33 tokens 1.27 / 1.15 / 1.03 /
+//   0.97, 128 tokens 1.14 / 0.95 / 0.94 / 0.88; packed, 128 tokens 1.09 / 1.01
+//   / 0.96 / 0.99.  H = 4096, F = 64, 64 experts (4096 down units), packed, 160
+//   tokens: 164 us against 130.
+// Up to 128 tokens both kernels add the same two K parts in the same order,
+// and from 128 on both layouts take the same one, so the layouts' results are
+// equal bit for bit from 33 tokens on (and up to 16; between, k_share).
+bool wide_applies(const FfnArgs& a) {
+  if (a.B <= (a.packed ? 96 : 32)) return false;
+  if (a.B > (a.packed ? 127 : 64)) return a.F >= 128 || n_blocks(a, 1, 64) <= 1024;
+  return a.F >= 256 && n_blocks(a, 0, 64) >= 256;
+}
 
 hipError_t launch_ffn_bf16(const FfnArgs& a, hipStream_t s) {
   if (a.B <= 4) return launch_bf16_pair<S2MOE_BF16_TINY>(a, s);
   if (a.B <= 16) return launch_bf16_pair<S2MOE_BF16_SMALL>(a, s);
-  if (a.B > (a.packed ? kWideMinPacked : kWideMinRows)) return launch_ffn_bf16_wide(a, s);
+  if (wide_applies(a)) return launch_ffn_bf16_wide(a, s);
   if (a.B <= 32) return launch_bf16_pair<S2MOE_BF16_MEDIUM>(a, s);
-  return launch_bf16_pair<S2MOE_BF16_LARGE>(a, s);
+  return launch_bf16_large(a, s);
 }
 
 }  // namespace s2moe
