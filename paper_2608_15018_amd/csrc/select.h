@@ -9,10 +9,13 @@ namespace s2moe {
 
 // Total-order key of a float: larger value -> larger key.  -0 is folded
 // into +0 first so that equal values tie (and then break on the index).
-// Finite values map to keys >= 0x00800000, so 0 can mark an empty slot.
+// Finite values map to keys >= 0x00800000, so 0 can mark an empty slot.  The
+// negative NaNs whose keys would be below 0x00010000 (bf16 of all bits set
+// among them) take that key: wave_top_k could not tell them from empty slots
+// by their upper halves, and would select those too.
 __device__ __forceinline__ uint32_t order_key(float v) {
   uint32_t u = __float_as_uint(v + 0.0f);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  return max(0x00010000u, (u & 0x80000000u) ? ~u : (u | 0x80000000u));
 }
 
 __device__ __forceinline__ float key_value(uint32_t k) {

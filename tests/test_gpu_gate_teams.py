@@ -79,3 +79,35 @@ def test_ranking_inside_the_gating_launch(E, k, B, hidden, act):
     assert_same_bits(one, four, label)
     ref = oracle.forward(d["x"], d["router"], d["conf_w"], d["experts"], d["shared"], shape)
     check_routing(one, ref, label)
+
+
+# A token whose logits are all the NaN of all bits set (in fp32 or in bf16, so
+# with a key of 0 or 0xFFFF but for the clamp): it still gets k experts, and the
+# other tokens' plain ranking is theirs (g, and so a biased selection, is NaN
+# for the whole batch).  By maxima and by search, in the small-batch gate, one
+# token a wave, and rows.
+@pytest.mark.parametrize("bits", [-1, -0x10000])
+@pytest.mark.parametrize("E,k,B,alpha", [(64, 3, 2, 0.0), (64, 12, 2, 0.0), (40, 3, 6, 0.5),
+                                         (40, 9, 6, 0.5), (200, 4, 20, 0.5), (200, 12, 40, 0.5)])
+def test_nan_logits_still_select_k_experts(E, k, B, alpha, bits):
+    import paper_2608_15018_amd as s2
+    H = -(-E // 64) * 64
+    rng = np.random.default_rng(E + k)
+    x = np.zeros((B, H), np.float32)
+    x[:, :E] = rng.permuted(np.tile(np.arange(E), (B, 1)), axis=1) / 8.0
+    r = oracle.route(x, np.eye(E, H, dtype=np.float32), k, "f32")
+    x[1] = np.array([bits], np.int32).view(np.float32)[0]
+    log(f"[gate] NaN row E={E} k={k} B={B}")
+    L = s2.make_layer(hidden=H, ffn=64, n_experts=E, top_k=k, cap=k, alpha=alpha, act="f32",
+                      wdt="f32")
+    rt = s2.Routing(L, B)
+    s2.route(L, torch.from_numpy(x).cuda(), torch.eye(E, H).cuda(), rt)
+    s2.reuse_gate(L, torch.ones(B).cuda(), rt)
+    torch.cuda.synchronize()
+    got = rt.host()
+    for n in ("plain_idx", "idx"):
+        assert (np.diff(got[n], axis=1) > 0).all() and got[n].min() >= 0 and got[n].max() < E, n
+    others = np.arange(B) != 1
+    np.testing.assert_array_equal(got["plain_idx"][others], r["plain_idx"][others])
+    assert got["count"].sum() == B * k
+    np.testing.assert_array_equal(np.sort(got["slot"]), np.arange(B * k))
