@@ -167,12 +167,15 @@ def _ptr(t) -> int | None:
     return t.data_ptr()
 
 
+# torch.cuda.current_stream() builds a Stream object: 2.6 us of a call's 17 at
+# the smallest layer.  The handle alone is not public, so it may be absent.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
-        # torch.cuda.current_stream() builds a Stream object: 2.6 us of a
-        # call's 17 at the smallest layer.
-        if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream

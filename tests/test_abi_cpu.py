@@ -313,3 +313,16 @@ def test_moe_layer_validates_like_the_four_calls(lib):
     assert st == _lib.EINVAL and "gate_w" in msg
     st, msg = call(layer=_layer(cap=1))
     assert st == _lib.EINVAL and "cap" in msg
+
+
+@pytest.mark.parametrize("raw", [None, lambda device: 100 + device])
+def test_current_stream_with_and_without_the_raw_handle(monkeypatch, raw):
+    class Stream:
+        cuda_stream = 7
+
+    monkeypatch.setattr(_lib, "_raw_stream", raw)
+    monkeypatch.setattr(_lib.torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(_lib.torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(_lib.torch.cuda, "current_stream", Stream)
+    assert _lib._stream(None) == (7 if raw is None else 103)
+    assert _lib._stream(5) == 5
