@@ -63,7 +63,7 @@ CASES = [
     ("B8 (four calls)", _shape(), 8, False),
     ("int4 B2", _shape(wdt="q4g32"), 2, True),
     ("fp32 B1 (four calls)", _shape(act="f32", wdt="f32"), 1, False),
-    ("B16 E8 (route_kernel)", _shape(cap=4, alpha=0.5), 16, False),
+    ("B16 E8 (ranked in the gate)", _shape(cap=4, alpha=0.5), 16, False),
     ("int4 e64 k3 B4 shared", _shape(hidden=512, ffn=256, n_experts=64, top_k=3, cap=3,
                                      n_shared=2, ffn_shared=256, wdt="q4g32"), 4, True),
     ("int4 e128 k3 B1 F1024", _shape(hidden=512, ffn=1024, n_experts=128, top_k=3, cap=3,
@@ -76,6 +76,7 @@ CASES = [
     ("int4 B16 K parts", _shape(ffn=8192, cap=4, alpha=0.5, wdt="q4g32"), 16, False),
     ("int4 B12 E96 K parts rows", _shape(hidden=128, ffn=4096, n_experts=96, cap=4, alpha=0.5,
                                          wdt="q4g32"), 12, False),
+    ("B16 E8 H1024 (route_kernel)", _shape(hidden=1024, cap=4, alpha=0.5), 16, False),
 ]
 
 
@@ -159,13 +160,13 @@ def test_moe_layer_equals_four_calls(case, packed):
 
 
 # (case, launches of one call, launches of the four calls).  Three on the
-# fused path; elsewhere the gating launch ranks the logits itself where the
-# routing would rank them in a launch of its own (B <= 8 or E > 64, logits
-# staged in LDS or a single-wave gate, up to 16 tokens), and with int4
-# weights the routing launch also converts x and the combine launch also
-# adds the down projection's K parts.
+# fused path; elsewhere the gating launch ranks the logits itself: in place of
+# a ranking launch of its own (B <= 8 or E > 64) one fewer, in place of the
+# ranking in route_kernel (whose logits are not sliced) as many.  With int4
+# weights the routing launch also converts x and the combine launch also adds
+# the down projection's K parts.
 LAUNCHES = [(1, 3, 6), (2, 3, 6), (8, 5, 6), (12, 3, 7), (14, 5, 5), (19, 6, 6), (15, 3, 7),
-            (18, 5, 7), (20, 5, 7), (21, 5, 8)]
+            (18, 5, 7), (20, 5, 7), (21, 5, 8), (22, 5, 5)]
 
 
 @pytest.mark.parametrize("case,n_call,n_four", LAUNCHES, ids=[CASES[c[0]][0] for c in LAUNCHES])
