@@ -100,8 +100,9 @@ s2moe_status check_layer(const char* fn, const s2moe_layer* L, int32_t B) {
 
 size_t round256(size_t n) { return (n + 255) & ~(size_t)255; }
 
-// Workspace: the SwiGLU activations Hh [B*k + S*B, max(F, F_s)] (fp32 for
-// fp32 weights, else 16-bit); for int4 weights then an fp16 copy of x and
+// Workspace: the SwiGLU activations Hh, B*k + S*B rows of max(F, F_s) (fp32 for
+// fp32 weights, else 16-bit; row-major, or in 32-wide steps where the bf16
+// kernel of large batches runs); for int4 weights then an fp16 copy of x and
 // the down projection's partial sums.
 size_t hh_rows(const s2moe_layer* L, int32_t B) {
   return (size_t)B * L->top_k + (size_t)L->n_shared * B;

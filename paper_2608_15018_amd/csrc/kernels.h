@@ -70,7 +70,8 @@ struct FfnArgs {
   const void *gate_s, *up_s, *down_s;
   const void *sh_gate, *sh_up, *sh_down;
   const void *sh_gate_s, *sh_up_s, *sh_down_s;
-  void* hh;  // workspace: SwiGLU activations [B*k + S*B, ldh] (fp32, bf16 or fp16)
+  void* hh;  // workspace: SwiGLU activations [B*k + S*B, ldh] (fp32, bf16 or fp16); where
+             // ffn_bf16_wide.hip runs, steps [ldh / 32][B*k + S*B][32] in the same bytes
   int ldh;
   void* x16;  // workspace, int4 weights only: x as fp16 [B, H] in the kernels' order
   float* part;  // workspace, int4 weights only: down partial sums of K parts 1..Q-1,
