@@ -237,8 +237,8 @@ s2moe_status s2moe_combine(const s2moe_layer *layer, int32_t n_tokens,
    first ranks the logits and buckets the batch itself; and the down
    projection with the combine folded in.  Every other batch runs the four
    calls' kernels one after another, except that the gating launch ranks
-   the logits itself where the routing would rank them in a launch of its
-   own, and that with Q4G32 weights the routing launch also makes the fp16
+   the logits itself (in place of a ranking launch, or of the ranking in the
+   routing launch) where that is faster, and that with Q4G32 weights the routing launch also makes the fp16
    copy of x and the combine launch also adds the down projection's K parts
    (two launches fewer than the four calls).  Layer dispatch cost dominates
    small batches (a draft step runs one per MoE layer and token).
