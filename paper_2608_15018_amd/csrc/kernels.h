@@ -225,8 +225,8 @@ bool route_ranks_separately(const RouteArgs& a);
 // the same terms in the same order.
 bool route_rows_same_bits(const RouteArgs& a);
 // launch_route then launch_reuse_gate, with the same results bit for bit;
-// where the routing ranks in a launch of its own, the gating launch ranks
-// the logits itself instead (gate.hip).
+// where it is faster, launch_route_rows and a gating launch that ranks the
+// logits itself (gate.hip).
 hipError_t launch_route_and_gate(const RouteArgs& ra, const GateArgs& a, hipStream_t s);
 hipError_t launch_stream_read(const void* src, size_t bytes, uint32_t* sink, int blocks,
                               hipStream_t s);
